@@ -235,6 +235,31 @@ hipError_t run_alternating(lbmrv_ctx* c, int kind_a, int kind_b, void* p, void* 
   return hipSuccess;
 }
 
+// nsteps steps p -> q of a two-array form on a grid that k_tile serves
+// (plan.steps >= 2), in an odd number of launches so that the last one ends in
+// q: the first reads pre-collision values at the node, the ones between gather
+// and keep post-collision values, the last one scatters pre-collision values.
+hipError_t run_tiles(const lbmrv_ctx* c, const TilePlan& plan, void* p, void* q, int64_t nsteps, int mode, double alpha,
+                     const float* ut, hipStream_t st) {
+  int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
+  if (launches % 2 == 0) ++launches;  // an even count has at least launches + 1 steps to share
+  StepLaunch L = base_launch(c, st);
+  L.kind = K_TILE;
+  L.mode = mode;
+  L.alpha = alpha;
+  L.ut = ut;
+  for (int64_t i = 0; i < launches; ++i) {
+    L.fin = i % 2 == 0 ? p : q;
+    L.fout = i % 2 == 0 ? q : p;
+    L.steps = (uint32_t)(nsteps / launches + (i < nsteps % launches ? 1 : 0));
+    L.gather = i > 0;
+    L.scatter = i + 1 == launches;
+    hipError_t e = kEntries[c->entry].step[c->sk](L);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // ---------------------------------------------------------------- run-time bases
 // Polynomials as dense coefficient vectors over a list of monomials.
 using Mono = std::array<int, 3>;
@@ -660,6 +685,21 @@ int lbmrv_step(lbmrv_ctx* c, void* f_in, void* f_out, int ut_mode, double ut_alp
                : LBMRV_ERR_HIP;
   }
   hipError_t e = hipSuccess;
+  // Both two-array forms give the same bits and both read and write both
+  // arrays, so without walls they share the cheaper routes: one step is one
+  // collide-and-scatter pass (the pull form's collision and transport are
+  // two), and more steps on a two-dimensional grid go several per launch.
+  if (!c->wall_mask) {
+    if (nsteps == 1) {
+      e = run_kind(c, K_PUSH, f_in, f_out, ut_mode, ut_alpha, ut_field, st);
+      return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
+    }
+    const TilePlan plan = c->d == 2 ? plan_tile(c->nx, c->ny) : TilePlan{};
+    if (plan.steps >= 2) {
+      e = run_tiles(c, plan, f_in, f_out, nsteps, ut_mode, ut_alpha, ut_field, st);
+      return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
+    }
+  }
   if (c->streaming == LBMRV_STREAM_PUSH) {
     // Pre-collision state throughout: one fused collide-and-scatter pass per
     // step.  Out-of-place passes alternate between the two buffers, so an odd

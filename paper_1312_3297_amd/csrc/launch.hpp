@@ -8,6 +8,7 @@
 
 #include "adjoint.hpp"
 #include "kernels.hpp"
+#include "multistep.hpp"
 
 namespace lbmrv {
 
@@ -31,6 +32,9 @@ struct StepLaunch {
   uint32_t xcd_remap; // block order (see block_tile)
   hipStream_t stream;
   int block;   // threads per block along x
+  // K_TILE (two-dimensional lattices): several steps per launch
+  uint32_t steps;            // steps of this launch
+  uint32_t gather, scatter;  // as in TileArgs
 };
 
 struct MomLaunch {
@@ -55,8 +59,8 @@ constexpr size_t lds_for_blocks(size_t n) {
 }
 static_assert(lds_for_blocks(4) == 36 * 1024 && lds_for_blocks(3) == 44 * 1024, "LDS reservations");
 
-template <class B, int ST, int MODE, int KIND, int RLX>
-hipError_t launch_step_t(const StepLaunch& L) {
+template <int ST>
+StepArgs<typename Store<ST>::T> step_args(const StepLaunch& L) {
   using T = typename Store<ST>::T;
   StepArgs<T> a{};
   a.fin = L.fin;
@@ -76,6 +80,13 @@ hipError_t launch_step_t(const StepLaunch& L) {
   a.xcd_remap = L.xcd_remap;
   for (int f = 0; f < 6; ++f)
     for (int ax = 0; ax < 3; ++ax) a.wall_coef[f][ax] = T(L.wall_coef[f][ax]);
+  return a;
+}
+
+template <class B, int ST, int MODE, int KIND, int RLX>
+hipError_t launch_step_t(const StepLaunch& L) {
+  using T = typename Store<ST>::T;
+  StepArgs<T> a = step_args<ST>(L);
   // D3Q19 with FP16 storage, even in-place step: node pairs (k_aa_even_pair),
   // up to 128 pairs of a row per block and as many rows as fill 256 threads
   if constexpr (ST == 2 && KIND == K_AA_EVEN && B::Q == 19) {
@@ -138,8 +149,34 @@ hipError_t launch_step_t(const StepLaunch& L) {
   return hipGetLastError();
 }
 
+template <class B, int ST, int MODE, int RLX>
+hipError_t launch_tile_t(const StepLaunch& L) {
+  if constexpr (B::Lat::D == 2) {
+    const TilePlan p = plan_tile(L.nx, L.ny);
+    if (L.steps < 1 || L.steps > p.steps) return hipErrorInvalidValue;
+    TileArgs g{};
+    g.steps = L.steps;
+    g.t[0] = p.t[0];
+    g.t[1] = p.t[1];
+    g.gather = L.gather;
+    g.scatter = L.scatter;
+    for (uint32_t s = 0; s < L.steps; ++s) {
+      const uint32_t e = p.t[0] + 2 * (L.steps - 1 - s);
+      g.m[s] = ((1u << 18) + e - 1) / e;
+    }
+    StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
+    dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], 1);
+    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+    return hipGetLastError();
+  } else {
+    return hipErrorInvalidValue;
+  }
+}
+
 template <class B, int ST, int MODE>
 hipError_t launch_step_m(const StepLaunch& L) {
+  if (L.kind == K_TILE)
+    return L.relax ? launch_tile_t<B, ST, MODE, 1>(L) : launch_tile_t<B, ST, MODE, 0>(L);
   if (L.relax) {  // run-time basis: the two-array forms
     switch (L.kind) {
       case K_PULL: return launch_step_t<B, ST, MODE, K_PULL, 1>(L);

@@ -1,0 +1,92 @@
+"""Several time steps per launch against the single relaxation and transport.
+
+lbmrv_collide followed by lbmrv_transport is the general path: one kernel each,
+any grid.  The step call must give the same bits whatever number of steps its
+launches fuse, on both sides of every rule that picks a tile (the tolerance is
+zero: every node does the same arithmetic and rounds to the storage type at
+every step in both).
+"""
+import numpy as np
+import pytest
+
+from paper_1312_3297_amd import workloads
+from paper_1312_3297_amd.lbmrv import Lbmrv
+
+from _common import far_state, oracle_lattice, to_storage
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+RATES = {"d2q9": workloads.RATES_D2Q9_GROUPED, "d3q19": workloads.RATES_D3Q19, "d3q27": workloads.RATES_D3Q27}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def one_by_one(ctx, f, mode, field, nsteps):
+    """nsteps single relaxations and transports; the states after each."""
+    out, f = [], f.clone()
+    for _ in range(nsteps):
+        g = torch.empty_like(f)
+        ctx.collide(f, g, mode, 0.7, field)
+        ctx.transport(g, f)
+        out.append(f.clone())
+    return out
+
+
+def compare(lattice, shape, storage, mode, steps, basis="default", equilibrium="polynomial", rates=None,
+            streaming=("pull", "push"), order="auto"):
+    print("%s %s %s %s %s steps %s" % (lattice, shape, storage, mode, basis if isinstance(basis, str) else "run-time",
+                                      steps), flush=True)
+    lat = oracle_lattice(lattice, basis if basis == "geier" else "default")
+    st, _ = to_storage(lat, far_state(lat, shape, seed=41, amp=0.02, umax=0.08), storage)
+    f0 = torch.from_numpy(st).cuda()
+    field = None
+    if mode == "field":
+        rng = np.random.default_rng(42)
+        field = torch.from_numpy(rng.uniform(-0.1, 0.1, (lat.d,) + shape).astype(np.float32)).cuda()
+    ctx = Lbmrv(lattice, rates or RATES[lattice], tuple(reversed(shape)), storage, basis)
+    ctx.set_equilibrium(equilibrium)
+    ctx.set_block_order(order)
+    want = one_by_one(ctx, f0, mode, field, max(steps))
+    for kind in streaming:
+        ctx.set_streaming(kind)
+        for n in steps:
+            a, b = f0.clone(), torch.full_like(f0, float("nan"))
+            ctx.step(a, b, mode, 0.7, field, n)
+            torch.cuda.synchronize()
+            bits = torch.int16 if storage == "f16dev" else torch.int64 if storage == "f64" else torch.int32
+            assert torch.equal(b.view(bits), want[n - 1].view(bits)), (kind, n)
+
+
+# 2-D grids (ny, nx): around the smallest tiled extent, remainders of every
+# tile size, the thresholds between tile sizes (2^15 and 3 * 2^16 nodes), thin grids
+@pytest.mark.parametrize("shape", [(8, 40), (9, 9), (10, 300), (15, 16), (31, 33), (64, 64), (173, 190), (16, 2049),
+                                   (429, 458), (440, 450), (33, 6000), (36, 6001)])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32dev", "f16dev"])
+def test_tiles_equal_single_steps(shape, storage):
+    compare("d2q9", shape, storage, "fluid", (1, 2, 5, 8, 17), streaming=("pull",))
+
+
+@pytest.mark.parametrize("basis,mode,equilibrium", [("default", "field", "polynomial"), ("geier", "zero", "polynomial"),
+                                                    ("geier", "field", "maxwellian"), ("custom", "fluid", "polynomial"),
+                                                    ("custom", "field", "maxwellian")])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
+def test_tiles_in_every_mode_and_basis(basis, mode, equilibrium, storage):
+    b, rates = (workloads.RAW_D2Q9, workloads.RATES_RAW_D2Q9) if basis == "custom" else (basis, None)
+    for shape in ((21, 37), (190, 200), (450, 449)):
+        compare("d2q9", shape, storage, mode, (2, 7, 12), b, equilibrium, rates)
+
+
+@pytest.mark.parametrize("order", ["natural", "xcd"])
+def test_tiles_in_every_block_order(order):
+    compare("d2q9", (70, 95), "f32", "fluid", (9,), order=order)
+
+
+@pytest.mark.parametrize("lattice", ["d2q9", "d3q19", "d3q27"])
+@pytest.mark.parametrize("storage", ["f64", "f32dev", "f16dev"])
+def test_one_step_is_the_relaxation_and_the_transport(lattice, storage):
+    compare(lattice, (7, 70) if lattice == "d2q9" else (3, 5, 70), storage, "fluid", (1,))

@@ -10,6 +10,7 @@
 #include <array>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "lbmrv.h"
@@ -71,6 +72,7 @@ __global__ __launch_bounds__(kRedCols* kRedRows) void k_reduce_columns(const dou
 namespace {
 
 using StepFn = hipError_t (*)(const StepLaunch&);
+using PlanFn = TilePlan (*)(uint32_t, uint32_t, uint32_t);
 using AdjFn = hipError_t (*)(const AdjLaunch&);
 using FinFn = hipError_t (*)(void*, uint32_t, uint32_t, uint32_t, uint64_t, const FinArgs&, hipStream_t);
 using MomFn = hipError_t (*)(const MomLaunch&);
@@ -82,6 +84,7 @@ using DevScaleFn = hipError_t (*)(void*, uint64_t, const DevRef&, double, hipStr
 
 struct Entry {
   StepFn step[3];
+  PlanFn tile[3];
   MomFn mom[3];
   ConsFn cons[3];
   InitFn init[3];
@@ -96,6 +99,7 @@ struct Entry {
 #define LBMRV_ENTRY(NAME)                                                                 \
   Entry {                                                                                 \
     {launch_step_##NAME##_f64, launch_step_##NAME##_f32, launch_step_##NAME##_f16},       \
+        {plan_tile_##NAME##_f64, plan_tile_##NAME##_f32, plan_tile_##NAME##_f16},         \
         {launch_moments_##NAME##_f64, launch_moments_##NAME##_f32, launch_moments_##NAME##_f16}, \
         {launch_conserve_##NAME##_f64, launch_conserve_##NAME##_f32, launch_conserve_##NAME##_f16}, \
         {launch_init_##NAME##_f64, launch_init_##NAME##_f32, launch_init_##NAME##_f16},   \
@@ -258,6 +262,66 @@ hipError_t run_tiles(const lbmrv_ctx* c, const TilePlan& plan, void* p, void* q,
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// nsteps steps p -> q of a two-array form on a grid that k_slide serves: pairs
+// of steps, and as many single steps as leave an odd number of launches from
+// one array into the other (an in-place collision counts as none).
+hipError_t run_pairs(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int mode, double alpha, const float* ut,
+                     hipStream_t st) {
+  int64_t pairs = nsteps / 2, singles = nsteps % 2;
+  bool collided = false;  // the state in `cur` is post-collision
+  void *cur = p, *other = q;
+  hipError_t e;
+  auto push = [&]() -> hipError_t {
+    const hipError_t er = run_kind(c, K_PUSH, cur, other, mode, alpha, ut, st);
+    std::swap(cur, other);
+    return er;
+  };
+  if (singles == 1 && pairs % 2 == 1) {  // pairs alone end in q: collide in place first
+    if ((e = run_kind(c, K_COLLIDE, cur, cur, mode, alpha, ut, st)) != hipSuccess) return e;
+    collided = true;
+  } else if (singles == 1) {
+    if ((e = push()) != hipSuccess) return e;
+  } else if (pairs % 2 == 0) {  // one pair as two single steps
+    --pairs;
+    if ((e = push()) != hipSuccess || (e = push()) != hipSuccess) return e;
+  }
+  StepLaunch L = base_launch(c, st);
+  L.kind = K_SLIDE;
+  L.mode = mode;
+  L.alpha = alpha;
+  L.ut = ut;
+  // Neighbouring tiles share their ring nodes through L2, so they belong on one
+  // XCD at every size (D3Q19 256^3 FP32: 1.7 GB fetched per launch against 3.8
+  // in natural order, 593 against 735 us).
+  L.xcd_remap = c->block_order != LBMRV_ORDER_NATURAL;
+  for (int64_t i = 0; i < pairs; ++i) {
+    L.fin = cur;
+    L.fout = other;
+    L.gather = collided || i > 0;
+    L.scatter = i + 1 == pairs;
+    if ((e = kEntries[c->entry].step[c->sk](L)) != hipSuccess) return e;
+    std::swap(cur, other);
+  }
+  return hipSuccess;
+}
+
+// nsteps >= 2 steps p -> q of the two-array forms without walls by the kernels
+// that take several steps per launch; false (and nothing launched) if single
+// steps are the better choice on this grid.
+bool run_fused(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int mode, double alpha, const float* ut,
+               hipStream_t st, hipError_t& e) {
+  const TilePlan tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
+  if (tile.steps >= 2) {
+    e = run_tiles(c, tile, p, q, nsteps, mode, alpha, ut, st);
+    return true;
+  }
+  if (c->d == 3 && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) {
+    e = run_pairs(c, p, q, nsteps, mode, alpha, ut, st);
+    return true;
+  }
+  return false;
 }
 
 // ---------------------------------------------------------------- run-time bases
@@ -688,17 +752,14 @@ int lbmrv_step(lbmrv_ctx* c, void* f_in, void* f_out, int ut_mode, double ut_alp
   // Both two-array forms give the same bits and both read and write both
   // arrays, so without walls they share the cheaper routes: one step is one
   // collide-and-scatter pass (the pull form's collision and transport are
-  // two), and more steps on a two-dimensional grid go several per launch.
+  // two), and more steps go several per launch where the grid allows it.
   if (!c->wall_mask) {
     if (nsteps == 1) {
       e = run_kind(c, K_PUSH, f_in, f_out, ut_mode, ut_alpha, ut_field, st);
       return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
     }
-    const TilePlan plan = c->d == 2 ? plan_tile(c->nx, c->ny) : TilePlan{};
-    if (plan.steps >= 2) {
-      e = run_tiles(c, plan, f_in, f_out, nsteps, ut_mode, ut_alpha, ut_field, st);
+    if (run_fused(c, f_in, f_out, nsteps, ut_mode, ut_alpha, ut_field, st, e))
       return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
-    }
   }
   if (c->streaming == LBMRV_STREAM_PUSH) {
     // Pre-collision state throughout: one fused collide-and-scatter pass per

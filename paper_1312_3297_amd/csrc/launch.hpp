@@ -9,6 +9,7 @@
 #include "adjoint.hpp"
 #include "kernels.hpp"
 #include "multistep.hpp"
+#include "slide.hpp"
 
 namespace lbmrv {
 
@@ -32,9 +33,8 @@ struct StepLaunch {
   uint32_t xcd_remap; // block order (see block_tile)
   hipStream_t stream;
   int block;   // threads per block along x
-  // K_TILE (two-dimensional lattices): several steps per launch
-  uint32_t steps;            // steps of this launch
-  uint32_t gather, scatter;  // as in TileArgs
+  uint32_t steps;            // K_TILE: steps of this launch
+  uint32_t gather, scatter;  // K_TILE, K_SLIDE: as in TileArgs
 };
 
 struct MomLaunch {
@@ -151,22 +151,34 @@ hipError_t launch_step_t(const StepLaunch& L) {
 
 template <class B, int ST, int MODE, int RLX>
 hipError_t launch_tile_t(const StepLaunch& L) {
-  if constexpr (B::Lat::D == 2) {
-    const TilePlan p = plan_tile(L.nx, L.ny);
-    if (L.steps < 1 || L.steps > p.steps) return hipErrorInvalidValue;
-    TileArgs g{};
-    g.steps = L.steps;
-    g.t[0] = p.t[0];
-    g.t[1] = p.t[1];
-    g.gather = L.gather;
-    g.scatter = L.scatter;
-    for (uint32_t s = 0; s < L.steps; ++s) {
-      const uint32_t e = p.t[0] + 2 * (L.steps - 1 - s);
-      g.m[s] = ((1u << 18) + e - 1) / e;
-    }
+  static_assert(tile_lds_bytes<B, ST, MODE>() <= kLdsPerCu, "the region of a tile fits in LDS");
+  const TilePlan p = plan_tile<B, ST>(L.nx, L.ny, L.nz);
+  if (L.steps < 1 || L.steps > p.steps) return hipErrorInvalidValue;
+  TileArgs g{};
+  g.steps = L.steps;
+  for (int a = 0; a < 3; ++a) g.t[a] = p.t[a];
+  g.gather = L.gather;
+  g.scatter = L.scatter;
+  for (uint32_t s = 0; s < L.steps; ++s) {
+    const uint32_t ring = L.steps - 1 - s, e = p.t[0] + 2 * ring, exy = e * (p.t[1] + 2 * ring);
+    g.mx[s] = ((1u << 18) + e - 1) / e;
+    g.mxy[s] = ((1u << 22) + exy - 1) / exy;
+  }
+  StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
+  dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.t[2] - 1) / p.t[2]);
+  hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+  return hipGetLastError();
+}
+
+template <class B, int ST, int MODE, int RLX>
+hipError_t launch_slide_t(const StepLaunch& L) {
+  if constexpr (B::Lat::D == 3 && ST != 2) {
+    const SlidePlan p = plan_slide(B::Q, sizeof(typename Store<ST>::S), L.nx, L.ny, L.nz);
+    if (!p.chunk) return hipErrorInvalidValue;
+    SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter};
     StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
-    dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], 1);
-    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+    dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.chunk - 1) / p.chunk);
+    hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX>), grid, dim3(SlideShape<B, ST>::threads), 0, L.stream, a, g);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -177,6 +189,8 @@ template <class B, int ST, int MODE>
 hipError_t launch_step_m(const StepLaunch& L) {
   if (L.kind == K_TILE)
     return L.relax ? launch_tile_t<B, ST, MODE, 1>(L) : launch_tile_t<B, ST, MODE, 0>(L);
+  if (L.kind == K_SLIDE)
+    return L.relax ? launch_slide_t<B, ST, MODE, 1>(L) : launch_slide_t<B, ST, MODE, 0>(L);
   if (L.relax) {  // run-time basis: the two-array forms
     switch (L.kind) {
       case K_PULL: return launch_step_t<B, ST, MODE, K_PULL, 1>(L);
@@ -394,6 +408,7 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
 // units (one unit per lattice and storage type, so they compile in parallel).
 #define LBMRV_DECLARE_LAUNCHERS(NAME, SKN)                                                  \
   hipError_t launch_step_##NAME##_##SKN(const StepLaunch& L);                               \
+  TilePlan plan_tile_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz);                 \
   hipError_t launch_moments_##NAME##_##SKN(const MomLaunch& L);                             \
   hipError_t launch_conserve_##NAME##_##SKN(const void* f, uint64_t N, double* partial,     \
                                             hipStream_t st);                                \
@@ -411,6 +426,9 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
 
 #define LBMRV_DEFINE_LAUNCHERS(NAME, BASIS, SKN, ST)                                        \
   hipError_t launch_step_##NAME##_##SKN(const StepLaunch& L) { return launch_step_s<BASIS, ST>(L); } \
+  TilePlan plan_tile_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz) {                \
+    return plan_tile<BASIS, ST>(nx, ny, nz);                                                \
+  }                                                                                         \
   hipError_t launch_moments_##NAME##_##SKN(const MomLaunch& L) {                            \
     return launch_moments_t<BASIS, ST>(L);                                                  \
   }                                                                                         \

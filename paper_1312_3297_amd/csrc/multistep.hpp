@@ -1,4 +1,4 @@
-// Several time steps per launch on two-dimensional lattices (k_tile).
+// Several time steps per launch, a tile at a time in LDS (k_tile).
 //
 // A single-step pass moves 2 q b bytes per node and step and costs a launch
 // of ~4 us however small the grid.  Here a workgroup takes a tile of nodes
@@ -18,93 +18,162 @@
 namespace lbmrv {
 
 constexpr int kTileMaxSteps = 8;
-// The LDS region (tile and ring) is kTileP x kTileP nodes.  A fixed pitch
-// makes every LDS offset of the unrolled population loops an immediate: with
-// run-time pitches the kernel spilled scalar registers and took 11.5 instead
-// of 9.7 us for eight steps of D2Q9 64^2 FP32.  40 x 40 FP32 nodes are 57.6 KB,
-// two workgroups per CU; a 48 x 48 region (one per CU) ran 20 % slower at
-// 1024^2, and FP64's 28 x 28 (two per CU) 5 % slower than its 40 x 40 (one).
-constexpr int kTileP = 40;
+
+// The region of k_tile (tile and ring), PX x PY x PZ nodes, and the most
+// threads of a workgroup (FP64 D3Q19 and D3Q27 need more than the 128 registers
+// that 1024 threads leave).  Fixed extents make every LDS offset of the unrolled
+// population loops an immediate: with run-time pitches the kernel spilled scalar
+// registers and took 11.5 instead of 9.7 us for eight steps of D2Q9 64^2 FP32.
+// 2-D: 40 x 40 FP32 nodes are 57.6 KB, two workgroups per CU; 48 x 48 (one per
+// CU) ran 20 % slower at 1024^2, and FP64's 28 x 28 (two per CU) 5 % slower than
+// its 40 x 40 (one).  3-D: with u~ a field 158 KB for D3Q19 FP32, 147 KB for
+// FP64, 146 KB for D3Q27 FP64, of the CU's 160.
+template <class B, int ST>
+struct TileShape {
+  static constexpr bool plane = B::Lat::D == 2, q27 = B::Q == 27;
+  static constexpr int PX = plane ? 40 : q27 ? 10 : ST == 0 ? 14 : 18;
+  static constexpr int PY = plane ? 40 : q27 || ST == 0 ? 8 : 10;
+  static constexpr int PZ = plane ? 1 : q27 || ST == 0 ? 8 : 10;
+  static constexpr int threads = !plane && (q27 || ST == 0) ? 512 : 1024;
+  static constexpr int nodes = PX * PY * PZ;
+};
 
 struct TileArgs {
   uint32_t steps;    // 1 .. kTileMaxSteps
-  uint32_t t[2];     // tile extents, t[a] + 2 (steps - 1) <= kTileP
+  uint32_t t[3];     // tile extents, t[a] + 2 (steps - 1) <= region extent
   uint32_t gather;   // 1: fin holds post-collision values, the first step gathers from x - c_j
   uint32_t scatter;  // 1: the last step stores at x + c_j (pre-collision result), 0: at the node
-  uint32_t m[kTileMaxSteps];  // step s: 2^18 / (t[0] + 2 (steps - 1 - s)), rounded up
+  // step s covers e = t + 2 (steps - 1 - s) nodes along each axis: reciprocals
+  // of e[0] (2^18 / e, rounded up) and of e[0] e[1] (2^22 / e, rounded up), exact
+  // for the node numbers of a region (below 2^18 / e[0] and 2^22 / (e[0] e[1]))
+  uint32_t mx[kTileMaxSteps];
+  uint32_t mxy[kTileMaxSteps];
 };
 
-// Tile and step count for an nx x ny grid; steps < 2: single steps are the
+// Tile and step count for a grid; steps < 2: single steps (or k_slide) are the
 // better choice.  The tile plus its ring must fit in one period of the grid
 // (t + steps - 1 <= extent), so that a coordinate wraps at most once.
 struct TilePlan {
-  uint32_t t[2];
+  uint32_t t[3];
   uint32_t steps;    // most steps per launch
   uint32_t threads;
 };
 
-inline TilePlan plan_tile(uint32_t nx, uint32_t ny) {
-  // Large tiles waste less on the ring (32 x 32, 5 steps: 27 % more node
-  // steps; 16 x 16: 57 %), small ones keep the 256 CUs busy on small grids.
-  // Measured, us per step, D2Q9 FP32 (one step per launch | 8 | 16 | 32):
-  //   64^2    3.6 | 1.2 |  -  |  -      256^2   4.0 |  2  | 1.6 |  -
-  //   512^2   4.8 |  -  | 3.6 | 2.8     2048^2 54.5 | 136 |  50 | 29.0
-  const uint64_t n = (uint64_t)nx * ny;
-  const uint32_t side = n >= 3u << 16 ? 32u : n >= 1u << 15 ? 16u : 8u;
-  const uint32_t most = side == 32u ? 5u : 8u;
-  const uint32_t lo = nx < ny ? nx : ny;
-  TilePlan p{};
-  if (lo <= side) return p;  // thinner than a tile: single steps
-  // equal tiles: no nearly empty last column or row
-  const uint32_t cx = (nx + side - 1) / side, cy = (ny + side - 1) / side;
-  p.t[0] = (nx + cx - 1) / cx;
-  p.t[1] = (ny + cy - 1) / cy;
-  const uint32_t t = p.t[0] > p.t[1] ? p.t[0] : p.t[1];
-  p.steps = lo - t + 1 < most ? lo - t + 1 : most;
-  // one workgroup per CU wants a thread per region node, two share the CU
-  p.threads = side == 32u ? ((uint64_t)cx * cy <= 256u ? 1024u : 768u) : side == 16u ? 768u : 512u;
-  return p;
+// Equal tiles of at most side[a] nodes (no nearly empty last row) and as many
+// steps, up to p.steps, as the ring leaves room for; false if fewer than two.
+inline bool fit_tile(TilePlan& p, int d, const uint32_t (&n)[3], const uint32_t (&side)[3]) {
+  for (int a = 0; a < d; ++a) {
+    const uint32_t c = (n[a] + side[a] - 1) / side[a];
+    p.t[a] = (n[a] + c - 1) / c;
+    if (p.t[a] + p.steps - 1 > n[a]) p.steps = n[a] - p.t[a] + 1;
+  }
+  if (p.steps < 2) p.steps = 0;
+  return p.steps != 0;
+}
+
+template <class B, int ST>
+TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
+  using Sh = TileShape<B, ST>;
+  const uint32_t n[3] = {nx, ny, nz};
+  const uint64_t nodes = (uint64_t)nx * ny * nz;
+  TilePlan p{{1, 1, 1}, 0, 0};
+  if constexpr (B::Lat::D == 2) {
+    // Large tiles waste less on the ring (32 x 32, 5 steps: 27 % more node
+    // steps; 16 x 16: 57 %), small ones keep the 256 CUs busy on small grids.
+    // Measured, us per step, D2Q9 FP32 (one step per launch | 8 | 16 | 32):
+    //   64^2    3.6 | 1.2 | 1.5 |  -      256^2   4.0 |  2  | 1.6 | 2.5
+    //   512^2   4.8 |  -  | 3.6 | 2.8     2048^2 54.5 | 136 |  50 | 27.5
+    const uint32_t s = nodes >= 3u << 16 ? 32u : nodes >= 1u << 15 ? 16u : 8u;
+    p.steps = s == 32u ? 5u : 8u;
+    fit_tile(p, 2, n, {s, s, 1u});
+    // one workgroup per CU wants a thread per region node, two share the CU
+    const uint64_t groups = (uint64_t)((nx + p.t[0] - 1) / p.t[0]) * ((ny + p.t[1] - 1) / p.t[1]);
+    p.threads = s == 32u ? (groups <= 256u ? 1024u : 768u) : s == 16u ? 768u : 512u;
+    return p;
+  } else {
+    // In space the ring is dear (16 x 8 x 8, two steps: 38 % more node steps;
+    // 4 x 4 x 4, three: 4.2 times as many), which only pays while a pass is bound
+    // by its launch and latency: the smallest tile that at most 256 workgroups,
+    // one per CU, cover the grid with, and no such tile beyond that.  Measured, us
+    // per step, single | fused:
+    //   D3Q19 FP32  16^3 5.1 | 2.6  32^3 5.2 | 3.2  48^3 5.9 | 5.0  64^3 9.0 | 7.0
+    //   D3Q19 FP64  16^3 6.5 | 3.0  32^3 6.0 | 4.4  48^3 10.4 | 7.3
+    //   D3Q27 FP32  16^3 6.0 | 4.2  32^3 5.5 | 4.8  48^3 7.2 | 7.4
+    struct Side {
+      uint32_t s[3];
+      uint32_t steps;
+    };
+    constexpr bool f64 = ST == 0, q27 = B::Q == 27;
+    const Side sides[4] = {{{4, 4, 4}, q27 ? 2u : 3u},
+                           {{8, 4, 4}, q27 || f64 ? 2u : 4u},
+                           {{12, 6, 6}, 2u},
+                           {{16, 8, 8}, 2u}};
+    for (const Side& c : sides) {
+      const uint32_t r = 2 * (c.steps - 1);
+      if (c.s[0] + r > (uint32_t)Sh::PX || c.s[1] + r > (uint32_t)Sh::PY || c.s[2] + r > (uint32_t)Sh::PZ) break;
+      // FP16 gains nothing beyond 12 x 6 x 6 (64^3: 7.0 against 7.5 us per step)
+      if (ST == 2 && c.s[0] > 12u) break;
+      uint64_t groups = 1;
+      for (int a = 0; a < 3; ++a) groups *= (n[a] + c.s[a] - 1) / c.s[a];
+      if (groups > 256) continue;
+      p.steps = c.steps;
+      if (!fit_tile(p, 3, n, c.s)) return p;
+      const uint32_t q = 2 * (p.steps - 1), region = (p.t[0] + q) * (p.t[1] + q) * (p.t[2] + q);
+      const uint32_t most = Sh::threads;
+      p.threads = region > 1024u ? 768u : (region + 63) / 64 * 64;
+      if (p.threads > most) p.threads = most;
+      return p;
+    }
+    (void)nodes;
+    return p;
+  }
 }
 
 template <class B, int ST, int MODE>
 constexpr size_t tile_lds_bytes() {
-  constexpr size_t R = kTileP * kTileP;
+  constexpr size_t R = TileShape<B, ST>::nodes;
   constexpr size_t f = (B::Q * R * sizeof(typename Store<ST>::S) + 15) / 16 * 16;
   return f + (MODE == UT_FIELD ? B::Lat::D * R * sizeof(float) : 0);
 }
 
 template <class B, int ST, int MODE, int RLX>
-__global__ __launch_bounds__(1024) void k_tile(StepArgs<typename Store<ST>::T> a, TileArgs g) {
+__global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<typename Store<ST>::T> a, TileArgs g) {
   using L = typename B::Lat;
   using S = typename Store<ST>::S;
   using T = typename Store<ST>::T;
+  using Sh = TileShape<B, ST>;
   constexpr int Q = B::Q;
   constexpr int D = L::D;
-  constexpr int P = kTileP, R = P * P;
-  static_assert(D == 2, "two-dimensional lattices");
+  constexpr int P = Sh::PX, P2 = Sh::PX * Sh::PY, R = Sh::nodes;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   S* lf = reinterpret_cast<S*>(lds_raw);
   float* lu = reinterpret_cast<float*>(lds_raw + tile_lds_bytes<B, ST, UT_ZERO>());
 
-  const int nx = (int)a.nx, ny = (int)a.ny;
+  const int nx = (int)a.nx, ny = (int)a.ny, nz = (int)a.nz;
   const uint64_t N = a.N;
   const S* fin = static_cast<const S*>(a.fin);
   S* fout = static_cast<S*>(a.fout);
   const uint3 tile = block_tile(a.xcd_remap);
   const int steps = (int)g.steps;
-  const int x0 = (int)(tile.x * g.t[0]), y0 = (int)(tile.y * g.t[1]);
+  const int x0 = (int)(tile.x * g.t[0]), y0 = (int)(tile.y * g.t[1]), z0 = (int)(tile.z * g.t[2]);
 
   for (int s = 0; s < steps; ++s) {
     const int ring = steps - 1 - s;
-    const uint32_t ex = g.t[0] + 2 * ring, ey = g.t[1] + 2 * ring;
-    const uint32_t count = ex * ey;
-    const uint32_t m = g.m[s];
+    const uint32_t ex = g.t[0] + 2 * ring, exy = ex * (g.t[1] + 2 * ring);
+    const uint32_t count = D == 3 ? exy * (g.t[2] + 2 * ring) : exy;
+    const uint32_t mx = g.mx[s], mxy = g.mxy[s];
     for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) {
-      const uint32_t iy = __umul24(i, m) >> 18, ix = i - __umul24(iy, ex);
-      const int l = (int)__umul24(iy + s, P) + (int)ix + s;
+      uint32_t iz = 0, r = i;
+      if constexpr (D == 3) {
+        iz = __umul24(i, mxy) >> 22;
+        r = i - __umul24(iz, exy);
+      }
+      const uint32_t iy = __umul24(r, mx) >> 18, ix = r - __umul24(iy, ex);
+      int l = (int)__umul24(iy + s, P) + (int)ix + s;
+      if constexpr (D == 3) l += (int)__umul24(iz + s, P2);
       T h[Q];
       T utf[3] = {T(0), T(0), T(0)};
-      int x = 0, y = 0;
+      int x = 0, y = 0, z = 0;
       bool inside = false;
       if (s == 0 || ring == 0) {
         x = x0 - ring + (int)ix;
@@ -114,27 +183,52 @@ __global__ __launch_bounds__(1024) void k_tile(StepArgs<typename Store<ST>::T> a
         x -= x >= nx ? nx : 0;
         y += y < 0 ? ny : 0;
         y -= y >= ny ? ny : 0;
+        if constexpr (D == 3) {
+          z = z0 - ring + (int)iz;
+          inside = inside && z < nz;
+          z += z < 0 ? nz : 0;
+          z -= z >= nz ? nz : 0;
+        }
       }
+      // node offset of x + dir c_j, or the node itself where the launch does not shift
+      auto node = [&](auto jj, auto dirc, int shifted) -> uint32_t {
+        constexpr int cx = decltype(dirc)::value * L::c[jj].x, cy = decltype(dirc)::value * L::c[jj].y,
+                      cz = decltype(dirc)::value * L::c[jj].z;
+        int xx = x, yy = y, zz = z;
+        if (shifted) {
+          if constexpr (cx > 0) xx = x == nx - 1 ? 0 : x + 1;
+          if constexpr (cx < 0) xx = x == 0 ? nx - 1 : x - 1;
+          if constexpr (cy > 0) yy = y == ny - 1 ? 0 : y + 1;
+          if constexpr (cy < 0) yy = y == 0 ? ny - 1 : y - 1;
+          if constexpr (cz > 0) zz = z == nz - 1 ? 0 : z + 1;
+          if constexpr (cz < 0) zz = z == 0 ? nz - 1 : z - 1;
+        }
+        return D == 3 ? ((uint32_t)zz * ny + (uint32_t)yy) * nx + (uint32_t)xx : (uint32_t)yy * nx + (uint32_t)xx;
+      };
       if (s == 0) {
-        const int gs = g.gather ? 1 : 0;
-        const int xm = gs ? (x == 0 ? nx - 1 : x - 1) : x, xp = gs ? (x == nx - 1 ? 0 : x + 1) : x;
-        const uint32_t r0 = (uint32_t)y * nx, rm = gs ? (uint32_t)(y == 0 ? ny - 1 : y - 1) * nx : r0,
-                       rp = gs ? (uint32_t)(y == ny - 1 ? 0 : y + 1) * nx : r0;
+        const int shifted = g.gather ? 1 : 0;
+        // the population's base moves on by an opaque stride: as loop invariants
+        // the 2 Q bases of fin and fout overflow the scalar registers
+        uint64_t stride = N;
+        asm volatile("" : "+s"(stride));
+        const S* pop = fin;
         sfor<Q>([&](auto jj) {
-          constexpr int cx = L::c[jj].x, cy = L::c[jj].y;
-          const uint32_t n = (cy > 0 ? rm : cy < 0 ? rp : r0) + (uint32_t)(cx > 0 ? xm : cx < 0 ? xp : x);
-          h[jj] = T(fin[(uint64_t)jj * N + n]);
+          h[jj] = T(pop[node(jj, std::integral_constant<int, -1>{}, shifted)]);
+          pop += stride;
         });
         if constexpr (MODE == UT_FIELD) {
+          const uint32_t own = node(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, 0);
           sfor<D>([&](auto al) {
-            const float v = a.ut[(uint64_t)al * N + r0 + x];
+            const float v = a.ut[(uint64_t)al * N + own];
             lu[al * R + l] = v;
             utf[al] = T(v) * a.inv_lambda;
           });
         }
       } else {
         if (s & 1) {
-          sfor<Q>([&](auto jj) { h[jj] = T(lf[l + (opposite<L>(jj) * R - L::c[jj].y * P - L::c[jj].x)]); });
+          sfor<Q>([&](auto jj) {
+            h[jj] = T(lf[l + (opposite<L>(jj) * R - L::c[jj].z * P2 - L::c[jj].y * P - L::c[jj].x)]);
+          });
         } else {
           sfor<Q>([&](auto jj) { h[jj] = T(lf[l + jj * R]); });
         }
@@ -151,18 +245,17 @@ __global__ __launch_bounds__(1024) void k_tile(StepArgs<typename Store<ST>::T> a
       sfor<Q>([&](auto jj) { o[jj] = S(h[jj]); });
       if (ring == 0) {
         if (inside) {
-          const int gs = g.scatter ? 1 : 0;
-          const int xm = gs ? (x == 0 ? nx - 1 : x - 1) : x, xp = gs ? (x == nx - 1 ? 0 : x + 1) : x;
-          const uint32_t r0 = (uint32_t)y * nx, rm = gs ? (uint32_t)(y == 0 ? ny - 1 : y - 1) * nx : r0,
-                         rp = gs ? (uint32_t)(y == ny - 1 ? 0 : y + 1) * nx : r0;
+          const int shifted = g.scatter ? 1 : 0;
+          uint64_t stride = N;
+          asm volatile("" : "+s"(stride));
+          S* pop = fout;
           sfor<Q>([&](auto jj) {
-            constexpr int cx = L::c[jj].x, cy = L::c[jj].y;
-            const uint32_t n = (cy < 0 ? rm : cy > 0 ? rp : r0) + (uint32_t)(cx < 0 ? xm : cx > 0 ? xp : x);
-            fout[(uint64_t)jj * N + n] = o[jj];
+            pop[node(jj, std::integral_constant<int, 1>{}, shifted)] = o[jj];
+            pop += stride;
           });
         }
       } else if (s & 1) {
-        sfor<Q>([&](auto jj) { lf[l + (jj * R + L::c[jj].y * P + L::c[jj].x)] = o[jj]; });
+        sfor<Q>([&](auto jj) { lf[l + (jj * R + L::c[jj].z * P2 + L::c[jj].y * P + L::c[jj].x)] = o[jj]; });
       } else {
         sfor<Q>([&](auto jj) { lf[l + opposite<L>(jj) * R] = o[jj]; });
       }

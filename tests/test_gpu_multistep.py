@@ -81,9 +81,43 @@ def test_tiles_in_every_mode_and_basis(basis, mode, equilibrium, storage):
         compare("d2q9", shape, storage, mode, (2, 7, 12), b, equilibrium, rates)
 
 
+# 3-D grids (nz, ny, nx): every tile of the rule (up to 256 workgroups of each),
+# extents equal to and one above a tile's, the first grid beyond the tiles, and
+# extents too small for any
+@pytest.mark.parametrize("lattice", ["d3q19", "d3q27"])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
+@pytest.mark.parametrize("shape", [(4, 4, 4), (5, 6, 7), (8, 8, 9), (3, 17, 20), (24, 25, 26), (17, 30, 33),
+                                   (47, 48, 49), (64, 64, 61)])
+def test_tiles_in_space_equal_single_steps(lattice, storage, shape):
+    compare(lattice, shape, storage, "field" if shape[0] % 2 else "fluid", (2, 3, 4, 7), streaming=("pull",))
+
+
+# two steps per launch on 3-D grids: chunks of one plane count and with a short
+# last one, tiles that divide an extent and that leave a remainder, few planes;
+# the last of each list is below the bound on idle columns (single steps)
+PAIRS = {"d3q19": [(70, 64, 64), (5, 161, 193), (131, 31, 64), (16, 97, 128), (301, 17, 33)],
+         "d3q27": [(80, 80, 81), (101, 77, 66), (7, 305, 257), (900, 24, 28)]}
+
+
+@pytest.mark.parametrize("lattice", ["d3q19", "d3q27"])
+@pytest.mark.parametrize("storage,mode", [("f64", "field"), ("f32", "fluid"), ("f32dev", "zero")])
+def test_pairs_equal_single_steps(lattice, storage, mode):
+    for shape in PAIRS[lattice]:
+        compare(lattice, shape, storage, mode, (2, 3, 4, 5, 8), streaming=("pull",))
+
+
+@pytest.mark.parametrize("lattice,storage,shape", [("d3q19", "f32", (40, 64, 64)), ("d3q19", "f64", (6, 9, 20)),
+                                                   ("d3q27", "f32", (80, 80, 81)), ("d3q27", "f64", (9, 8, 10))])
+def test_run_time_bases_in_space(lattice, storage, shape):
+    basis, rates = {"d3q19": (workloads.RAW2_D3Q19, workloads.RATES_RAW2_D3Q19),
+                    "d3q27": (workloads.HERMITE_D3Q27, workloads.RATES_HERMITE_D3Q27)}[lattice]
+    compare(lattice, shape, storage, "fluid", (2, 5), basis, "maxwellian", rates, streaming=("push",))
+
+
 @pytest.mark.parametrize("order", ["natural", "xcd"])
-def test_tiles_in_every_block_order(order):
-    compare("d2q9", (70, 95), "f32", "fluid", (9,), order=order)
+@pytest.mark.parametrize("lattice,shape", [("d2q9", (70, 95)), ("d3q19", (20, 21, 40)), ("d3q19", (70, 64, 64))])
+def test_every_block_order(lattice, shape, order):
+    compare(lattice, shape, "f32", "fluid", (9,), order=order)
 
 
 @pytest.mark.parametrize("lattice", ["d2q9", "d3q19", "d3q27"])

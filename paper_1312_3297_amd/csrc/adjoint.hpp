@@ -39,7 +39,53 @@ struct AdjArgs {
   const T* rnninv;  // and its inverse
   uint32_t xcd_remap;  // block order, as for the step kernels (block_tile)
   uint32_t eq_maxwell; // 1: equilibrium moments of the continuous Maxwellian
+  uint32_t rnx, rny;   // k_adjoint: floor(2^32 / nx) and floor(2^32 / ny), at most 2^32 - 1
 };
+
+// n / d and n mod d from r = min(floor(2^32 / d), 2^32 - 1): the estimate
+// umulhi(n, r) is the quotient or one less, for every 32-bit n.
+__device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t r, uint32_t& rem) {
+  uint32_t q = __umulhi(n, r);
+  rem = n - q * d;
+  if (rem >= d) {
+    rem -= d;
+    ++q;
+  }
+  return q;
+}
+
+// Sums over the wavefront of V values per lane, in a fixed order: at each of
+// the first steps a lane keeps half of the values and takes the partner's
+// contributions to them, so V values cost about V exchanges instead of 6 V.
+// Value k ends up in the lanes l with k = sum_i bit(l, 5 - i) 2^(H - 1 - i) over
+// the first H = log2 V steps (V a power of two up to 64); sum_slot(l) gives k
+// and whether lane l is the one that writes it.
+template <int V>
+__device__ __forceinline__ double wave_sums(double (&v)[V], int lane) {
+  static_assert((V & (V - 1)) == 0 && V <= 64);
+  constexpr int H = __builtin_ctz(V);
+  sfor<6>([&](auto ii) {
+    constexpr int m = 32 >> ii;
+    if constexpr (ii < H) {
+      constexpr int half = V >> (ii + 1);
+      const bool upper = (lane & m) != 0;
+      sfor<half>([&](auto kk) {
+        const double lo = v[kk], hi = v[kk + half];
+        v[kk] = (upper ? hi : lo) + __shfl_xor(upper ? lo : hi, m);
+      });
+    } else {
+      v[0] += __shfl_xor(v[0], m);
+    }
+  });
+  return v[0];
+}
+template <int V>
+__device__ __forceinline__ int sum_slot(int lane, bool& writes) {
+  constexpr int H = __builtin_ctz(V);
+  writes = (lane & ((64 >> H) - 1)) == 0;
+  return lane >> (6 - H);
+}
+constexpr int pow2_at_least(int n) { return n <= 1 ? 1 : 2 * pow2_at_least((n + 1) / 2); }
 
 // The adjoint of one time step at one node (the transpose of the collision
 // Jacobian, with the equations at the top of this file): from the node's
@@ -394,25 +440,38 @@ __device__ __forceinline__ void adjoint_node(const AdjArgs<typename Store<ST>::T
 
 }
 
+// One reverse step.  A workgroup takes 256 consecutive nodes of the grid,
+// whatever its rows: with workgroups along one row a 64-wide grid left 192 of
+// 256 threads without a node of their own (D3Q19 64^3 FP32: 53 us a step).
+// D3Q19 with FP32 arithmetic and u~ = u took 129 registers, one past the 128
+// that let a SIMD hold four of its wavefronts, so four are asked for.
+template <class B, int ST>
+constexpr int adjoint_min_waves() {
+  return B::Q == 19 && ST != 0 ? 4 : 1;
+}
+
 template <class B, int ST, int MODE, int RLX>
-__global__ __launch_bounds__(256) void k_adjoint(AdjArgs<typename Store<ST>::T> a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adjoint_min_waves<B, ST>()))) void k_adjoint(
+    AdjArgs<typename Store<ST>::T> a) {
   using L = typename B::Lat;
   using S = typename Store<ST>::S;
   using T = typename Store<ST>::T;
   constexpr int Q = B::Q;
   constexpr int D = L::D;
 
-  const uint3 tile = block_tile(a.xcd_remap);
-  const uint32_t xr = tile.x * blockDim.x + threadIdx.x;
-  const bool active = xr < a.nx;
-  const uint32_t x = active ? xr : a.nx - 1;  // inactive lanes recompute a valid node, store nothing
-  const uint32_t y = tile.y, z = tile.z;
+  const uint32_t bid = block_tile(a.xcd_remap).x;
+  const uint64_t N = a.N;
+  const uint64_t n64 = (uint64_t)bid * 256u + threadIdx.x;
+  const bool active = n64 < N;
+  const uint32_t own = (uint32_t)(active ? n64 : N - 1);  // inactive lanes recompute a valid node, store nothing
   const uint32_t nx = a.nx, ny = a.ny, nz = a.nz;
+  uint32_t x, y = 0, z = 0;
+  const uint32_t row = div_by(own, nx, a.rnx, x);
+  if constexpr (D == 3) z = div_by(row, ny, a.rny, y);
+  else y = row;
   const uint32_t xp = x == nx - 1 ? 0 : x + 1, xm = x == 0 ? nx - 1 : x - 1;
   const uint32_t yp = y == ny - 1 ? 0 : y + 1, ym = y == 0 ? ny - 1 : y - 1;
   const uint32_t zp = z == nz - 1 ? 0 : z + 1, zm = z == 0 ? nz - 1 : z - 1;
-  const uint32_t own = (z * ny + y) * nx + x;
-  const uint64_t N = a.N;
   const S* f = static_cast<const S*>(a.f);
 
   T h[Q], g[Q];
@@ -443,25 +502,25 @@ __global__ __launch_bounds__(256) void k_adjoint(AdjArgs<typename Store<ST>::T> 
     sfor<Q>([&](auto jj) { __builtin_nontemporal_store(lam[jj], &a.lam_out[(uint64_t)jj * N + own]); });
   }
 
-  // dJ/ds_k: block sum of z3_k r_k in FP64, added to this block's row
-  __shared__ double red[4][Q];
+  // dJ/ds_k: block sum of z3_k r_k in FP64, added to this block's row (one row
+  // per range of nodes, not per workgroup, so the sums do not depend on the
+  // block order)
+  constexpr int NC = Q - D - 1, V = pow2_at_least(NC);
+  __shared__ double red[4][V];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // one row per tile (not per workgroup), so the sums do not depend on the block order
-  const uint32_t bid = tile.x + gridDim.x * (tile.y + gridDim.y * tile.z);
-  sfor<Q>([&](auto kk) {
-    constexpr int K = kk;
-    if constexpr (K > D) {
-      double c = active ? double(z3[K]) * double(r[K]) : 0.0;
-      for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-      if (lane == 0) red[wave][K] = c;
-    }
+  double c[V];
+  sfor<V>([&](auto kk) {
+    if constexpr (kk < NC) c[kk] = active ? double(z3[D + 1 + kk]) * double(r[D + 1 + kk]) : 0.0;
+    else c[kk] = 0.0;
   });
+  bool writes;
+  const int slot = sum_slot<V>(lane, writes);
+  const double sum = wave_sums<V>(c, lane);
+  if (writes) red[wave][slot] = sum;
   __syncthreads();
-  if (threadIdx.x < Q && (int)threadIdx.x > D) {
-    double sum = 0.0;
-    const int nw = (blockDim.x + 63) >> 6;
-    for (int w = 0; w < nw; ++w) sum += red[w][threadIdx.x];
-    a.partial[(uint64_t)bid * Q + threadIdx.x] += sum;
+  if (threadIdx.x < NC) {
+    const int k = threadIdx.x;
+    a.partial[(uint64_t)bid * Q + D + 1 + k] += (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
   }
 }
 
@@ -499,7 +558,7 @@ __global__ __launch_bounds__(kA2X* kA2Y) void k_adjoint2(AdjArgs<typename Store<
   __shared__ T lh[Q][kA2HY * kA2HX];  // lambda^{n+1}, halo region
   __shared__ T lr[Q][kA2RY * kA2RX];  // lambda^n, ring region
   __shared__ T gr[D][NT];             // step n's dJ/du~ at the owned nodes (field mode)
-  __shared__ double red[NT / 64][Q];
+  __shared__ double red[NT / 64][pow2_at_least(Q - D - 1)];
 
   const uint3 tile = block_tile(a.xcd_remap);
   const int tid = threadIdx.x;
@@ -582,21 +641,23 @@ __global__ __launch_bounds__(kA2X* kA2Y) void k_adjoint2(AdjArgs<typename Store<
   }
 
   // dJ/ds_k: block sum, added to this tile's row
+  constexpr int NC = Q - D - 1, V = pow2_at_least(NC);
   const int lane = tid & 63, wave = tid >> 6;
-  sfor<Q>([&](auto kk) {
-    constexpr int K = kk;
-    if constexpr (K > D) {
-      double c = sacc[K];
-      for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-      if (lane == 0) red[wave][K] = c;
-    }
+  double c[V];
+  sfor<V>([&](auto kk) {
+    if constexpr (kk < NC) c[kk] = sacc[D + 1 + kk];
+    else c[kk] = 0.0;
   });
+  bool writes;
+  const int slot = sum_slot<V>(lane, writes);
+  const double total = wave_sums<V>(c, lane);
+  if (writes) red[wave][slot] = total;
   __syncthreads();
-  if (tid < Q && tid > D) {
+  if (tid < NC) {
     double sum = 0.0;
     for (int w = 0; w < NT / 64; ++w) sum += red[w][tid];
     const uint32_t bid = tile.x + gridDim.x * (tile.y + gridDim.y * tile.z);
-    a.partial[(uint64_t)bid * Q + tid] += sum;
+    a.partial[(uint64_t)bid * Q + D + 1 + tid] += sum;
   }
 }
 

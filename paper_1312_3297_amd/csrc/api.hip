@@ -1049,8 +1049,7 @@ AdjPlan adj_plan(const lbmrv_ctx* c, int64_t nsteps, int64_t K) {
   p.nsets = p.nseg < 3 ? p.nseg : 3;
   p.state_bytes = align256(elem_bytes(c->storage) * c->q * c->N);
   p.lam_bytes = align256((c->storage == LBMRV_F64 ? 8 : 4) * (size_t)c->q * c->N);
-  const uint64_t gx = (c->nx + c->block - 1) / c->block;
-  p.nblocks = gx * c->ny * c->nz;
+  p.nblocks = (c->N + 255) / 256;  // rows of k_adjoint's workgroups
   if (has_adjoint2(c->d, c->sk)) {  // rows of the two-step kernel's tiles
     const uint64_t n2 = (uint64_t)((c->nx + kA2X - 1) / kA2X) * ((c->ny + kA2Y - 1) / kA2Y);
     if (n2 > p.nblocks) p.nblocks = n2;

@@ -334,9 +334,11 @@ hipError_t launch_adjoint_t(const AdjLaunch& L) {
   a.rnninv = static_cast<const T*>(L.rnninv);
   a.xcd_remap = L.xcd_remap;
   a.eq_maxwell = L.eq_maxwell;
-  const int bx = L.block;
-  dim3 grid((L.nx + bx - 1) / bx, L.ny, L.nz);
-  hipLaunchKernelGGL((k_adjoint<B, ST, MODE, RLX>), grid, dim3(bx), 0, L.stream, a);
+  auto reciprocal = [](uint32_t d) { return d == 1u ? 0xffffffffu : (uint32_t)((1ull << 32) / d); };
+  a.rnx = reciprocal(L.nx);
+  a.rny = reciprocal(L.ny);
+  const dim3 grid((unsigned)((L.N + 255) / 256));
+  hipLaunchKernelGGL((k_adjoint<B, ST, MODE, RLX>), grid, dim3(256), 0, L.stream, a);
   return hipGetLastError();
 }
 

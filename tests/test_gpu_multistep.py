@@ -124,3 +124,26 @@ def test_every_block_order(lattice, shape, order):
 @pytest.mark.parametrize("storage", ["f64", "f32dev", "f16dev"])
 def test_one_step_is_the_relaxation_and_the_transport(lattice, storage):
     compare(lattice, (7, 70) if lattice == "d2q9" else (3, 5, 70), storage, "fluid", (1,))
+
+
+@pytest.mark.parametrize("shape", [(4, 8, 8), (2, 3, 43), (1, 1, 257), (5, 1, 51), (3, 2, 171)])
+@pytest.mark.parametrize("mode", ["fluid", "field"])
+def test_reverse_step_over_whole_rows(shape, mode):
+    """The reverse step's workgroups take 256 consecutive nodes whatever the
+    rows: one full workgroup, one or two nodes in the last one, rows longer and
+    shorter than a workgroup, against the FP64 adjoint oracle (1e-10 normwise:
+    both sides FP64, different order of operations over a few steps)."""
+    from oracle import adjoint as E
+    lat = oracle_lattice("d3q19")
+    rng = np.random.default_rng(43)
+    f0 = far_state(lat, shape, seed=44, amp=0.02, umax=0.05)
+    field = rng.uniform(-0.1, 0.1, (3,) + shape).astype(np.float32).astype(np.float64) if mode == "field" else None
+    cot = rng.standard_normal(f0.shape)
+    _, gf, gs, gu = E.vjp(lat, f0, RATES["d3q19"], 3, cot, field=field, alpha=0.9 if mode == "fluid" else None)
+    ctx = Lbmrv("d3q19", RATES["d3q19"], tuple(reversed(shape)), "f64")
+    gpu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    _, gfg, gsg, gug = ctx.adjoint(gpu(f0), gpu(cot), 3, 2, mode, None if field is None else gpu(field.astype(np.float32)),
+                                   alpha=0.9)
+    torch.cuda.synchronize()
+    for got, ref in ((gfg, gf), (gsg, gs)) + (((gug, gu),) if mode == "field" else ()):
+        assert np.abs(got.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()

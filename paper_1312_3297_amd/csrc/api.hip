@@ -239,13 +239,26 @@ hipError_t run_alternating(lbmrv_ctx* c, int kind_a, int kind_b, void* p, void* 
   return hipSuccess;
 }
 
-// nsteps steps p -> q of a two-array form on a grid that k_tile serves
-// (plan.steps >= 2), in an odd number of launches so that the last one ends in
+// The kernel that takes several steps per launch on this grid, and how many;
+// steps < 2: none does.
+struct Fused {
+  int kind;
+  int64_t steps;
+};
+Fused fused_kind(const lbmrv_ctx* c) {
+  const TilePlan tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
+  if (tile.steps >= 2) return {K_TILE, tile.steps};
+  if (c->d == 3 && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) return {K_SLIDE, 2};
+  return {K_PUSH, 1};
+}
+
+// nsteps steps p -> q of a two-array form on a grid that k_tile serves (`most`
+// steps per launch), in an odd number of launches so that the last one ends in
 // q: the first reads pre-collision values at the node, the ones between gather
 // and keep post-collision values, the last one scatters pre-collision values.
-hipError_t run_tiles(const lbmrv_ctx* c, const TilePlan& plan, void* p, void* q, int64_t nsteps, int mode, double alpha,
+hipError_t run_tiles(const lbmrv_ctx* c, int64_t most, void* p, void* q, int64_t nsteps, int mode, double alpha,
                      const float* ut, hipStream_t st) {
-  int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
+  int64_t launches = (nsteps + most - 1) / most;
   if (launches % 2 == 0) ++launches;  // an even count has at least launches + 1 steps to share
   StepLaunch L = base_launch(c, st);
   L.kind = K_TILE;
@@ -312,16 +325,76 @@ hipError_t run_pairs(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int m
 // steps are the better choice on this grid.
 bool run_fused(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int mode, double alpha, const float* ut,
                hipStream_t st, hipError_t& e) {
-  const TilePlan tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
-  if (tile.steps >= 2) {
-    e = run_tiles(c, tile, p, q, nsteps, mode, alpha, ut, st);
-    return true;
+  const Fused f = fused_kind(c);
+  if (f.kind == K_TILE) e = run_tiles(c, f.steps, p, q, nsteps, mode, alpha, ut, st);
+  else if (f.kind == K_SLIDE) e = run_pairs(c, p, q, nsteps, mode, alpha, ut, st);
+  return f.kind != K_PUSH;
+}
+
+// n >= 1 steps src -> dst, pre-collision states, for callers that own other
+// arrays: the values between the launches go to buf[0] and buf[1] in turn.
+hipError_t run_advance(const lbmrv_ctx* c, const void* src, void* dst, int64_t n, void* const (&buf)[2], int mode,
+                       double alpha, const float* ut, hipStream_t st) {
+  const Fused f = fused_kind(c);
+  StepLaunch L = base_launch(c, st);
+  L.mode = mode;
+  L.alpha = alpha;
+  L.ut = ut;
+  if (f.kind == K_SLIDE) L.xcd_remap = c->block_order != LBMRV_ORDER_NATURAL;
+  // K_SLIDE takes exactly two steps: an odd count starts with a single one
+  const bool single = f.kind == K_PUSH || (f.kind == K_SLIDE && n % 2 == 1) || n == 1;
+  const int64_t launches = f.kind == K_PUSH ? n : f.kind == K_SLIDE ? n / 2 + n % 2 : (n + f.steps - 1) / f.steps;
+  const void* from = src;
+  bool post = false;  // `from` holds post-collision values
+  for (int64_t i = 0; i < launches; ++i) {
+    const bool last = i + 1 == launches;
+    L.fin = from;
+    L.fout = last ? dst : buf[i % 2];
+    if (f.kind == K_PUSH || (single && i == 0)) {
+      L.kind = K_PUSH;
+      post = false;
+    } else {
+      L.kind = f.kind;
+      L.steps = f.kind == K_TILE ? (uint32_t)(n / launches + (i < n % launches ? 1 : 0)) : 2u;
+      L.gather = post;
+      L.scatter = last;
+      post = true;
+    }
+    hipError_t e = kEntries[c->entry].step[c->sk](L);
+    if (e != hipSuccess) return e;
+    from = L.fout;
   }
-  if (c->d == 3 && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) {
-    e = run_pairs(c, p, q, nsteps, mode, alpha, ut, st);
-    return true;
+  return hipSuccess;
+}
+
+// n >= 1 steps from state(0), every state kept: state(t) is where state t
+// belongs, and states 1 .. n - 1 lie keep_bytes apart.
+template <class State>
+hipError_t run_keeping(const lbmrv_ctx* c, State state, int64_t n, size_t keep_bytes, int mode, double alpha,
+                       const float* ut, hipStream_t st) {
+  const Fused f = fused_kind(c);
+  StepLaunch L = base_launch(c, st);
+  L.mode = mode;
+  L.alpha = alpha;
+  L.ut = ut;
+  L.gather = 0;
+  L.scatter = 1;
+  L.keep_stride = keep_bytes / elem_bytes(c->storage);
+  if (f.kind == K_SLIDE) L.xcd_remap = c->block_order != LBMRV_ORDER_NATURAL;
+  const int64_t launches = (n + f.steps - 1) / f.steps;
+  int64_t t = 0;
+  for (int64_t i = 0; i < launches; ++i) {
+    const int64_t k = n / launches + (i < n % launches ? 1 : 0);
+    L.kind = k == 1 ? K_PUSH : f.kind;
+    L.steps = (uint32_t)k;
+    L.keep = k == 1 ? nullptr : state(t + 1);
+    L.fin = state(t);
+    L.fout = state(t + k);
+    hipError_t e = kEntries[c->entry].step[c->sk](L);
+    if (e != hipSuccess) return e;
+    t += k;
   }
-  return false;
+  return hipSuccess;
 }
 
 // ---------------------------------------------------------------- run-time bases
@@ -1151,12 +1224,9 @@ int lbmrv_adjoint(lbmrv_ctx* c, const void* f0, int ut_mode, double ut_alpha, co
     if (t % K == 0) return snaps + P.state_bytes * (t / K - 1);
     return segs + P.state_bytes * (P.nsegslots * ((t / K) % S) + (t % K - 1));
   };
-  // state t in the forward sweep: states inside earlier segments are not kept,
-  // they alternate between two buffers that stay in the last-level cache
-  auto fwd_state = [&](int64_t t) -> void* {
-    if (t == 0 || t == nsteps || t % K == 0 || t / K == last) return state(t);
-    return pingpong + P.state_bytes * (t % 2);
-  };
+  // values between the launches of the forward sweep over earlier segments,
+  // whose states are not kept: two buffers that stay in the last-level cache
+  void* const between[2] = {pingpong, pingpong + P.state_bytes};
   const Entry& E = kEntries[c->entry];
   hipError_t e;
   // Recompute the states inside segment r from its first state on st2, into
@@ -1165,25 +1235,27 @@ int lbmrv_adjoint(lbmrv_ctx* c, const void* f0, int ut_mode, double ut_alpha, co
   auto issue_recompute = [&](int64_t r) -> hipError_t {
     hipError_t er;
     if (r + S <= last && (er = hipStreamWaitEvent(st2, ev_rev(r + S), 0)) != hipSuccess) return er;
-    const int64_t t0 = r * K, t1 = (t0 + K < nsteps) ? t0 + K : nsteps;
-    for (int64_t t = t0; t + 1 < t1; ++t)
-      if ((er = run_kind(c, K_PUSH, state(t), state(t + 1), ut_mode, ut_alpha, ut_field, st2)) != hipSuccess)
-        return er;
+    const int64_t t0 = r * K;  // r < last: K steps, of which K - 1 states are missing
+    if (K > 1 && (er = run_keeping(c, [&](int64_t t) { return state(t0 + t); }, K - 1, P.state_bytes, ut_mode, ut_alpha,
+                                   ut_field, st2)) != hipSuccess)
+      return er;
     return hipEventRecord(ev_rec(r), st2);
   };
   // forward sweep (scatter form, pre-collision states), keeping every K-th
   // state and the states of the last segment.  The S - 1 segments before the
   // last (whose sets the forward sweep does not touch) are recomputed on st2
   // as soon as their first state is written, alongside the rest of the sweep.
-  for (int64_t t = 0; t < nsteps; ++t) {
-    e = run_kind(c, K_PUSH, fwd_state(t), fwd_state(t + 1), ut_mode, ut_alpha, ut_field, st);
-    if (e != hipSuccess) return LBMRV_ERR_HIP;
-    const int64_t r = (t + 1) / K;
-    if (recompute_any && (t + 1) % K == 0 && r < last && r >= last - (S - 1)) {
+  for (int64_t r = 0; r <= last; ++r) {
+    const int64_t t0 = r * K;
+    if (recompute_any && r > 0 && r < last && r >= last - (S - 1)) {
       if (hipEventRecord(ev_snap, st) != hipSuccess || hipStreamWaitEvent(st2, ev_snap, 0) != hipSuccess ||
           issue_recompute(r) != hipSuccess)
         return LBMRV_ERR_HIP;
     }
+    e = r < last ? run_advance(c, state(t0), state(t0 + K), K, between, ut_mode, ut_alpha, ut_field, st)
+                 : run_keeping(c, [&](int64_t t) { return state(t0 + t); }, nsteps - t0, P.state_bytes, ut_mode,
+                               ut_alpha, ut_field, st);
+    if (e != hipSuccess) return LBMRV_ERR_HIP;
   }
   if (recompute_any && last - (S - 1) <= 0 && last >= 1) {
     // segment 0 among them: its first state is f0, present from the start

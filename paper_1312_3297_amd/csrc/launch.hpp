@@ -33,8 +33,10 @@ struct StepLaunch {
   uint32_t xcd_remap; // block order (see block_tile)
   hipStream_t stream;
   int block;   // threads per block along x
-  uint32_t steps;            // K_TILE: steps of this launch
+  uint64_t steps;            // K_TILE: steps of this launch
   uint32_t gather, scatter;  // K_TILE, K_SLIDE: as in TileArgs
+  void* keep;                // K_TILE, K_SLIDE: as in TileArgs
+  uint64_t keep_stride;      // K_TILE: elements between kept states
 };
 
 struct MomLaunch {
@@ -155,18 +157,23 @@ hipError_t launch_tile_t(const StepLaunch& L) {
   const TilePlan p = plan_tile<B, ST>(L.nx, L.ny, L.nz);
   if (L.steps < 1 || L.steps > p.steps) return hipErrorInvalidValue;
   TileArgs g{};
-  g.steps = L.steps;
+  g.steps = (uint32_t)L.steps;
   for (int a = 0; a < 3; ++a) g.t[a] = p.t[a];
   g.gather = L.gather;
   g.scatter = L.scatter;
-  for (uint32_t s = 0; s < L.steps; ++s) {
-    const uint32_t ring = L.steps - 1 - s, e = p.t[0] + 2 * ring, exy = e * (p.t[1] + 2 * ring);
+  g.keep = L.keep;
+  g.keep_stride = L.keep_stride;
+  for (uint32_t s = 0; s < g.steps; ++s) {
+    const uint32_t ring = g.steps - 1 - s, e = p.t[0] + 2 * ring, exy = e * (p.t[1] + 2 * ring);
     g.mx[s] = ((1u << 18) + e - 1) / e;
     g.mxy[s] = ((1u << 22) + exy - 1) / exy;
   }
   StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
   dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.t[2] - 1) / p.t[2]);
-  hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+  if (L.keep)
+    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX, true>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+  else
+    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX, false>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
   return hipGetLastError();
 }
 
@@ -175,10 +182,13 @@ hipError_t launch_slide_t(const StepLaunch& L) {
   if constexpr (B::Lat::D == 3 && ST != 2) {
     const SlidePlan p = plan_slide(B::Q, sizeof(typename Store<ST>::S), L.nx, L.ny, L.nz);
     if (!p.chunk) return hipErrorInvalidValue;
-    SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter};
+    SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter, L.keep};
     StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
     dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.chunk - 1) / p.chunk);
-    hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX>), grid, dim3(SlideShape<B, ST>::threads), 0, L.stream, a, g);
+    if (L.keep)
+      hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, true>), grid, dim3(SlideShape<B, ST>::threads), 0, L.stream, a, g);
+    else
+      hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false>), grid, dim3(SlideShape<B, ST>::threads), 0, L.stream, a, g);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

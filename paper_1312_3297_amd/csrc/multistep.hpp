@@ -48,6 +48,8 @@ struct TileArgs {
   // for the node numbers of a region (below 2^18 / e[0] and 2^22 / (e[0] e[1]))
   uint32_t mx[kTileMaxSteps];
   uint32_t mxy[kTileMaxSteps];
+  void* keep;            // KEEP: where the states between the steps go, the state
+  uint64_t keep_stride;  // before step s (s >= 1) at keep + (s - 1) keep_stride, in elements
 };
 
 // Tile and step count for a grid; steps < 2: single steps (or k_slide) are the
@@ -136,7 +138,9 @@ constexpr size_t tile_lds_bytes() {
   return f + (MODE == UT_FIELD ? B::Lat::D * R * sizeof(float) : 0);
 }
 
-template <class B, int ST, int MODE, int RLX>
+// KEEP: the states between the steps are stored too (g.keep); an instance of
+// its own, as testing for it at every node cost the plain one 9 %.
+template <class B, int ST, int MODE, int RLX, bool KEEP>
 __global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<typename Store<ST>::T> a, TileArgs g) {
   using L = typename B::Lat;
   using S = typename Store<ST>::S;
@@ -175,10 +179,12 @@ __global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<t
       T utf[3] = {T(0), T(0), T(0)};
       int x = 0, y = 0, z = 0;
       bool inside = false;
-      if (s == 0 || ring == 0) {
+      if (KEEP || s == 0 || ring == 0) {
         x = x0 - ring + (int)ix;
         y = y0 - ring + (int)iy;
         inside = x < nx && y < ny;
+        // before the last step: nodes of the tile itself, not of its ring
+        if constexpr (KEEP) inside = inside && ix - ring < g.t[0] && iy - ring < g.t[1] && (D == 2 || iz - ring < g.t[2]);
         x += x < 0 ? nx : 0;
         x -= x >= nx ? nx : 0;
         y += y < 0 ? ny : 0;
@@ -234,6 +240,16 @@ __global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<t
         }
         if constexpr (MODE == UT_FIELD) {
           sfor<D>([&](auto al) { utf[al] = T(lu[al * R + l]) * a.inv_lambda; });
+        }
+        if (KEEP && inside) {
+          const uint32_t own = node(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, 0);
+          uint64_t stride = N;
+          asm volatile("" : "+s"(stride));
+          S* pop = static_cast<S*>(g.keep) + (uint64_t)(s - 1) * g.keep_stride;
+          sfor<Q>([&](auto jj) {
+            __builtin_nontemporal_store(S(h[jj]), &pop[own]);
+            pop += stride;
+          });
         }
       }
       collide_node<B, T, MODE, RLX>(h, a, utf);

@@ -331,10 +331,33 @@ bool run_fused(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int mode, d
   return f.kind != K_PUSH;
 }
 
+// n >= 1 steps p -> q (which may be the same array) on a grid of at most
+// kClosedNodes nodes.  One launch per kClosedSteps steps, so that none runs for
+// more than some ten milliseconds.
+constexpr int64_t kClosedSteps = 4096;
+hipError_t run_closed(const lbmrv_ctx* c, const void* p, void* q, int64_t nsteps, int mode, double alpha,
+                      const float* ut, hipStream_t st) {
+  StepLaunch L = base_launch(c, st);
+  L.kind = K_CLOSED;
+  L.mode = mode;
+  L.alpha = alpha;
+  L.ut = ut;
+  L.fin = p;
+  L.fout = q;
+  for (int64_t left = nsteps; left > 0; left -= kClosedSteps) {
+    L.steps = (uint64_t)(left < kClosedSteps ? left : kClosedSteps);
+    hipError_t e = kEntries[c->entry].step[c->sk](L);
+    if (e != hipSuccess) return e;
+    L.fin = q;
+  }
+  return hipSuccess;
+}
+
 // n >= 1 steps src -> dst, pre-collision states, for callers that own other
 // arrays: the values between the launches go to buf[0] and buf[1] in turn.
 hipError_t run_advance(const lbmrv_ctx* c, const void* src, void* dst, int64_t n, void* const (&buf)[2], int mode,
                        double alpha, const float* ut, hipStream_t st) {
+  if (c->N <= kClosedNodes) return run_closed(c, src, dst, n, mode, alpha, ut, st);
   const Fused f = fused_kind(c);
   StepLaunch L = base_launch(c, st);
   L.mode = mode;
@@ -796,6 +819,8 @@ int lbmrv_step(lbmrv_ctx* c, void* f_in, void* f_out, int ut_mode, double ut_alp
   if (c->custom && c->streaming == LBMRV_STREAM_AA) return LBMRV_ERR_UNSUPPORTED;
   if ((rc = check_device(c))) return rc;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  if (nsteps >= 1 && !c->wall_mask && c->N <= kClosedNodes)  // every form gives the same bits
+    return run_closed(c, f_in, f_out, nsteps, ut_mode, ut_alpha, ut_field, st) == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
   if (c->streaming == LBMRV_STREAM_AA) {
     // One array, in place: even steps collide at the node and store each
     // population in its opposite slot, odd steps gather from the opposite slots

@@ -77,9 +77,10 @@ enum Mode { UT_ZERO = 0, UT_FLUID = 1, UT_FIELD = 2 };
 // K_AA_ODD_WALLS  the same with half-way bounce-back walls on paired faces
 // K_TILE    several steps per launch, a tile at a time in LDS (k_tile)
 // K_SLIDE   two steps per launch, three-dimensional lattices (k_slide)
+// K_CLOSED  any number of steps per launch, the whole grid in one workgroup (k_closed)
 enum Kind {
   K_PULL = 0, K_PUSH = 1, K_COLLIDE = 2, K_STREAM = 3, K_AA_EVEN = 4, K_AA_ODD = 5, K_AA_ODD_WALLS = 6, K_TILE = 7,
-  K_SLIDE = 8
+  K_SLIDE = 8, K_CLOSED = 9
 };
 
 template <class T>

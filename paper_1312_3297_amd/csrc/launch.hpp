@@ -33,7 +33,7 @@ struct StepLaunch {
   uint32_t xcd_remap; // block order (see block_tile)
   hipStream_t stream;
   int block;   // threads per block along x
-  uint64_t steps;            // K_TILE: steps of this launch
+  uint64_t steps;            // K_TILE, K_CLOSED: steps of this launch
   uint32_t gather, scatter;  // K_TILE, K_SLIDE: as in TileArgs
   void* keep;                // K_TILE, K_SLIDE: as in TileArgs
   uint64_t keep_stride;      // K_TILE: elements between kept states
@@ -195,8 +195,20 @@ hipError_t launch_slide_t(const StepLaunch& L) {
   }
 }
 
+template <class B, int ST, int MODE, int RLX>
+hipError_t launch_closed_t(const StepLaunch& L) {
+  static_assert(closed_lds_bytes<B, ST, MODE>(kClosedNodes) <= kLdsPerCu, "the grid fits in LDS");
+  if (L.N > kClosedNodes || L.steps < 1) return hipErrorInvalidValue;
+  StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
+  hipLaunchKernelGGL((k_closed<B, ST, MODE, RLX>), dim3(1), dim3(((unsigned)L.N + 63) / 64 * 64),
+                     (closed_lds_bytes<B, ST, MODE>(L.N)), L.stream, a, L.steps);
+  return hipGetLastError();
+}
+
 template <class B, int ST, int MODE>
 hipError_t launch_step_m(const StepLaunch& L) {
+  if (L.kind == K_CLOSED)
+    return L.relax ? launch_closed_t<B, ST, MODE, 1>(L) : launch_closed_t<B, ST, MODE, 0>(L);
   if (L.kind == K_TILE)
     return L.relax ? launch_tile_t<B, ST, MODE, 1>(L) : launch_tile_t<B, ST, MODE, 0>(L);
   if (L.kind == K_SLIDE)

@@ -280,4 +280,70 @@ __global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<t
   }
 }
 
+// The whole grid in one workgroup, one thread per node, any number of steps in
+// one launch: for grids of at most kClosedNodes nodes, where k_tile would spend
+// most of its work on rings and still pay a launch every few steps.  The
+// populations stay in LDS in the in-place form of k_tile, wrapped; the last
+// step scatters to the natural layout.  Every load from fin comes before the
+// first store to fout, so the two may be the same array.  A step costs the
+// latency of one collision and one LDS exchange, which a second wavefront per
+// SIMD hides half of; D2Q9 16^2 FP64, 50 steps: 82 us by k_tile (7 launches).
+constexpr uint32_t kClosedNodes = 512;
+
+template <class B, int ST, int MODE>
+constexpr size_t closed_lds_bytes(size_t nodes) {
+  return (B::Q * nodes * sizeof(typename Store<ST>::S) + 15) / 16 * 16;
+}
+
+template <class B, int ST, int MODE, int RLX>
+__global__ __launch_bounds__(kClosedNodes) void k_closed(StepArgs<typename Store<ST>::T> a, uint64_t steps) {
+  using L = typename B::Lat;
+  using S = typename Store<ST>::S;
+  using T = typename Store<ST>::T;
+  constexpr int Q = B::Q;
+  constexpr int D = L::D;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  S* lf = reinterpret_cast<S*>(lds_raw);
+
+  const uint32_t nx = a.nx, ny = a.ny, nz = a.nz, n = (uint32_t)a.N;
+  const bool active = threadIdx.x < n;
+  const uint32_t own = active ? threadIdx.x : n - 1;  // idle threads start from the last node and write nothing
+  const uint32_t x = own % nx, row = own / nx, y = D == 3 ? row % ny : row, z = D == 3 ? row / ny : 0;
+  const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+  const uint32_t ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+  const uint32_t zm = z == 0 ? nz - 1 : z - 1, zp = z == nz - 1 ? 0 : z + 1;
+  uint32_t at[Q];  // slot j of node x + c_j
+  sfor<Q>([&](auto jj) {
+    constexpr int cx = L::c[jj].x, cy = L::c[jj].y, cz = L::c[jj].z;
+    const uint32_t xx = cx > 0 ? xp : cx < 0 ? xm : x, yy = cy > 0 ? yp : cy < 0 ? ym : y, zz = cz > 0 ? zp : cz < 0 ? zm : z;
+    at[jj] = jj * n + (zz * ny + yy) * nx + xx;
+  });
+
+  const S* fin = static_cast<const S*>(a.fin);
+  S* fout = static_cast<S*>(a.fout);
+  T h[Q], utf[3] = {T(0), T(0), T(0)};
+  sfor<Q>([&](auto jj) { h[jj] = T(fin[jj * n + own]); });
+  if constexpr (MODE == UT_FIELD) {
+    sfor<D>([&](auto al) { utf[al] = T(a.ut[al * n + own]) * a.inv_lambda; });
+  }
+  S o[Q];
+  for (uint64_t s = 0;; ++s) {
+    collide_node<B, T, MODE, RLX>(h, a, utf);
+    sfor<Q>([&](auto jj) { o[jj] = S(h[jj]); });
+    if (s + 1 == steps) break;
+    const bool odd = (s & 1) != 0;
+    if (active) {
+      if (odd) sfor<Q>([&](auto jj) { lf[at[jj]] = o[jj]; });
+      else sfor<Q>([&](auto jj) { lf[opposite<L>(jj) * n + own] = o[jj]; });
+    }
+    __syncthreads();
+    if (active) {
+      if (odd) sfor<Q>([&](auto jj) { h[jj] = T(lf[jj * n + own]); });
+      else sfor<Q>([&](auto jj) { h[jj] = T(lf[at[opposite<L>(jj)]]); });
+    }
+  }
+  __syncthreads();  // one step: every load before the first store
+  if (active) sfor<Q>([&](auto jj) { fout[at[jj]] = o[jj]; });
+}
+
 }  // namespace lbmrv

@@ -147,3 +147,27 @@ def test_reverse_step_over_whole_rows(shape, mode):
     torch.cuda.synchronize()
     for got, ref in ((gfg, gf), (gsg, gs)) + (((gug, gu),) if mode == "field" else ()):
         assert np.abs(got.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("lattice,shape", [("d2q9", (1, 1)), ("d2q9", (1, 7)), ("d2q9", (16, 32)), ("d2q9", (19, 27)),
+                                           ("d3q19", (1, 2, 3)), ("d3q19", (8, 8, 8)), ("d3q27", (7, 8, 9))])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
+def test_small_grids_in_one_workgroup(lattice, shape, storage):
+    """Grids of up to 512 nodes (and the first beyond) run whole in one
+    workgroup, in place as well as between two arrays."""
+    for mode in ("fluid", "field"):
+        compare(lattice, shape, storage, mode, (1, 2, 7), streaming=("pull", "push", "aa"))
+    lat = oracle_lattice(lattice)
+    st, _ = to_storage(lat, far_state(lat, shape, seed=46, amp=0.02, umax=0.05), storage)
+    f = torch.from_numpy(st).cuda()
+    ctx = Lbmrv(lattice, RATES[lattice], tuple(reversed(shape)), storage)
+    ctx.set_streaming("aa")
+    for n in (1, 2, 5):
+        g = f.clone()
+        ctx.step(g, g, "fluid", 0.7, None, n)
+        torch.cuda.synchronize()
+        assert torch.equal(g, one_by_one(ctx, f, "fluid", None, n)[-1]), n
+
+
+def test_more_steps_than_one_launch_takes():
+    compare("d2q9", (3, 5), "f64", "fluid", (4096, 4097), streaming=("pull",))

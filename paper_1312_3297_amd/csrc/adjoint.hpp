@@ -111,11 +111,12 @@ __device__ __forceinline__ void adjoint_node(const AdjArgs<typename Store<ST>::T
   // ---- forward quantities at this node (monomial bases on {0, +-1}^d with
   // FP32 arithmetic: all moments, and below the two transposed maps, by the
   // cube passes of the forward kernel)
-  constexpr bool cube = CubeForm<B>::applies() && sizeof(T) == 4;
-  T mw[cube ? Q : 1];
+  constexpr bool cube = use_cube<B, T>(), pairs = use_pairs<B, T>();
+  T mw[cube || pairs ? Q : 1];
   if constexpr (cube) cube_moments<B>(h, mw);
+  else if constexpr (pairs) pair_moments<B, 0>(h, mw, RowsMW<B>{});
   T drho, jm[3] = {zsum<T>(), zsum<T>(), zsum<T>()};
-  if constexpr (cube) {
+  if constexpr (cube || pairs) {
     drho = mw[0];
     sfor<D>([&](auto al) { jm[al] = mw[1 + al]; });
   } else {
@@ -192,7 +193,7 @@ __device__ __forceinline__ void adjoint_node(const AdjArgs<typename Store<ST>::T
     constexpr int K = kk;
     if constexpr (K <= D) {
       v[K] = zsum<T>();
-    } else if constexpr (cube) {
+    } else if constexpr (cube || pairs) {
       mh[K] = mw[K];
     } else {
       mh[K] = zsum<T>();
@@ -312,6 +313,9 @@ __device__ __forceinline__ void adjoint_node(const AdjArgs<typename Store<ST>::T
   T zz[Q];  // z1 = M_W(0)^{-T} g, then z2 (in place through the shift)
   if constexpr (cube) {
     cube_populations_t<B>(g, zz);
+  } else if constexpr (pairs) {
+    sfor<D + 1>([&](auto kk) { zz[kk] = zsum<T>(); });
+    pair_moments<B, D + 1>(g, zz, RowsMWinvT<B>{});
   } else {
     sfor<Q>([&](auto kk) {
       constexpr int K = kk;
@@ -415,12 +419,13 @@ __device__ __forceinline__ void adjoint_node(const AdjArgs<typename Store<ST>::T
   if constexpr (MODE == UT_FLUID) {
     sfor<D>([&](auto al) { Bv[al] = fmac(a.alpha * irho, gut[al], Bv[al]); });
   }
-  T yt[cube ? Q : 1];  // M_W(0)^T z6
+  T yt[cube || pairs ? Q : 1];  // M_W(0)^T z6
   if constexpr (cube) cube_moments_t<B>(z5, yt);
+  else if constexpr (pairs) pair_populations<B>(z5, yt, RowsMWT<B>{});
   sfor<Q>([&](auto jj) {
     constexpr int J = jj;
     T yv = zsum<T>();
-    if constexpr (cube) {
+    if constexpr (cube || pairs) {
       yv = yt[J];
     } else {
       sfor<Tb::t.tMW[J].n>([&](auto i) { axpy_c<Tb::t.tMW[J].val[i]>(yv, z5[Tb::t.tMW[J].col[i]]); });

@@ -368,6 +368,119 @@ __device__ __forceinline__ void cube_populations_t(const T (&g)[B::Q], T (&zm)[B
   });
 }
 
+// ------------------------------------------------------------------ pair form
+// Bases that are no monomials (eq. (mom)), or whose cube form is not used: when
+// every W_k takes equal or opposite values on opposite velocities, M_W(0) acts
+// on the sums h_j + h_opp(j) alone (even k) or the differences alone (odd k),
+// its inverse gives an even and an odd part per pair, and both halves of a pair
+// share all of it.  For eq. (mom) on D2Q9 that is 32 + 37 operations for the two
+// maps instead of 54 + 57, each a sum over the same terms with the same
+// coefficients.  FP64 only: there the regrouping moves results by a few 1e-16
+// (D2Q9 by k_tile: 2048^2 52.7 -> 50.3 us a step, 64^2 1.30 -> 1.26), in FP32 it
+// moved the rate gradients of the adjoint, differences of nearly equal FP32
+// values, by 1e-2.
+template <class B>
+struct PairForm {
+  using L = typename B::Lat;
+  static constexpr int Q = B::Q;
+  // +1: W_k even under c -> -c, -1: odd, 0: neither
+  static constexpr int sign(int k) {
+    bool even = true, odd = true;
+    for (int j = 0; j < Q; ++j) {
+      even = even && Tab<B>::t.MW.m[k][opposite<L>(j)] == Tab<B>::t.MW.m[k][j];
+      odd = odd && Tab<B>::t.MW.m[k][opposite<L>(j)] == -Tab<B>::t.MW.m[k][j];
+    }
+    return even ? 1 : odd ? -1 : 0;
+  }
+  static constexpr bool applies() {
+    for (int k = 0; k < Q; ++k)
+      if (sign(k) == 0) return false;
+    return true;
+  }
+  // one of the two velocities of a pair stands for it
+  static constexpr bool leads(int j) { return j < opposite<L>(j); }
+};
+
+// m_k = sum_j M[k][j] h_j from the rows ROWS(k) of a map whose row k has the
+// parity of W_k; rows below K0 are left alone.
+template <class B, int K0, class T, class Rows>
+__device__ __forceinline__ void pair_moments(const T (&h)[B::Q], T (&m)[B::Q], Rows) {
+#pragma clang fp contract(on)  // as in collide_node
+  using L = typename B::Lat;
+  using P = PairForm<B>;
+  T s[B::Q], d[B::Q];
+  sfor<B::Q>([&](auto jj) {
+    if constexpr (P::leads(jj)) {
+      s[jj] = h[jj] + h[opposite<L>(jj)];
+      d[jj] = h[jj] - h[opposite<L>(jj)];
+    } else {
+      s[jj] = h[jj];
+      d[jj] = h[jj];
+    }
+  });
+  sfor<B::Q>([&](auto kk) {
+    constexpr int K = kk;
+    if constexpr (K >= K0) {
+      constexpr auto row = Rows::row(K);
+      T acc = zsum<T>();
+      sfor<row.n>([&](auto i) {
+        constexpr int j = row.col[i];
+        if constexpr (j == opposite<L>(j)) axpy_c<row.val[i]>(acc, h[j]);
+        else if constexpr (P::leads(j)) axpy_c<row.val[i]>(acc, P::sign(K) > 0 ? s[j] : d[j]);
+      });
+      m[K] = acc;
+    }
+  });
+}
+
+// y_j = sum_k A[j][k] z_k from the rows ROWS(j) of a map whose column k has the
+// parity of W_k.
+template <class B, class T, class Rows>
+__device__ __forceinline__ void pair_populations(const T (&z)[B::Q], T (&y)[B::Q], Rows) {
+#pragma clang fp contract(on)  // as in collide_node
+  using L = typename B::Lat;
+  using P = PairForm<B>;
+  sfor<B::Q>([&](auto jj) {
+    constexpr int J = jj;
+    if constexpr (P::leads(J) || J == opposite<L>(J)) {
+      constexpr auto row = Rows::row(J);
+      T even = zsum<T>(), odd = zsum<T>();
+      sfor<row.n>([&](auto i) {
+        if constexpr (P::sign(row.col[i]) > 0) axpy_c<row.val[i]>(even, z[row.col[i]]);
+        else axpy_c<row.val[i]>(odd, z[row.col[i]]);
+      });
+      if constexpr (P::leads(J)) {
+        y[J] = even + odd;
+        y[opposite<L>(J)] = even - odd;
+      } else {
+        y[J] = even;
+      }
+    }
+  });
+}
+
+// the rows of Tab<B> that the two maps take
+template <class B>
+struct RowsMW { static constexpr auto row(int k) { return Tab<B>::t.sMW[k]; } };
+template <class B>
+struct RowsMWinv { static constexpr auto row(int j) { return Tab<B>::t.sMWinv[j]; } };
+template <class B>
+struct RowsMWinvT { static constexpr auto row(int k) { return Tab<B>::t.tMWinv[k]; } };
+template <class B>
+struct RowsMWT { static constexpr auto row(int j) { return Tab<B>::t.tMW[j]; } };
+
+// Which form a lattice and arithmetic type use: the cube in FP32 (see
+// collide_node), pairs in two dimensions in FP64, sparse rows for the rest (in
+// three dimensions HBM bounds every FP64 kernel).
+template <class B, class T>
+constexpr bool use_cube() {
+  return CubeForm<B>::applies() && sizeof(T) == 4;
+}
+template <class B, class T>
+constexpr bool use_pairs() {
+  return sizeof(T) == 8 && B::Lat::D == 2 && PairForm<B>::applies();
+}
+
 // ------------------------------------------------------------------ collision
 // In-register collision at one node.  h holds the populations minus w_j rho0.
 // After return h holds the post-collision values (same offset).
@@ -390,15 +503,16 @@ __device__ __forceinline__ void collide_node(T (&h)[B::Q], const StepArgs<T>& a,
   // in three one-axis passes.  FP32 arithmetic only: with 8-byte values the
   // cube's live cells raise the register count (D3Q19: 96 -> 132 VGPRs, two
   // wavefronts per SIMD fewer), and the sparse rows measured 2.9 % faster.
-  constexpr bool cube = CubeForm<B>::applies() && sizeof(T) == 4;
-  T mw[cube ? Q : 1];
+  constexpr bool cube = use_cube<B, T>(), pairs = use_pairs<B, T>();
+  T mw[cube || pairs ? Q : 1];
   if constexpr (cube) cube_moments<B>(h, mw);
+  else if constexpr (pairs) pair_moments<B, 0>(h, mw, RowsMW<B>{});
 
   // conserved moments, eq. (rhoq): rho = rho0 + sum h, j = sum c h
   T drho, jm[3] = {zsum<T>(), zsum<T>(), zsum<T>()};
-  if constexpr (cube) {
+  if constexpr (cube || pairs) {
     drho = mw[0];
-    sfor<3>([&](auto al) { jm[al] = mw[1 + al]; });
+    sfor<D>([&](auto al) { jm[al] = mw[1 + al]; });
   } else {
     drho = h[0];
     sfor<Q - 1>([&](auto jj) { drho += h[jj + 1]; });
@@ -436,7 +550,7 @@ __device__ __forceinline__ void collide_node(T (&h)[B::Q], const StepArgs<T>& a,
     constexpr int K = kk;
     if constexpr (K <= D) {
       dl[K] = zsum<T>();
-    } else if constexpr (cube) {
+    } else if constexpr (cube || pairs) {
       mh[K] = mw[K];
     } else {
       mh[K] = zsum<T>();
@@ -579,6 +693,10 @@ __device__ __forceinline__ void collide_node(T (&h)[B::Q], const StepArgs<T>& a,
       if constexpr (c2 == 0) h[J] += dh[J];
       else h[J] = fmac(T(1.0 / (1 << c2)), dh[J], h[J]);
     });
+  } else if constexpr (pairs) {
+    T dh[Q];
+    pair_populations<B>(dl, dh, RowsMWinv<B>{});
+    sfor<Q>([&](auto jj) { h[jj] += dh[jj]; });
   } else {
     sfor<Q>([&](auto jj) {
       constexpr int J = jj;

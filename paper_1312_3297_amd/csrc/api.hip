@@ -246,6 +246,16 @@ struct Fused {
   int64_t steps;
 };
 Fused fused_kind(const lbmrv_ctx* c) {
+  if (c->wall_mask) {
+    // k_slide has walls on x and y faces, for the built-in bases; on both faces of
+    // an axis, as its last launch scatters (past a single wall, the slot a node
+    // bounces into would also be reached through the open face)
+    const uint32_t m = c->wall_mask;
+    const bool paired = (m & 1u) == ((m >> 1) & 1u) && ((m >> 2) & 1u) == ((m >> 3) & 1u);
+    const bool serves = c->d == 3 && !(m >> 4) && paired && !c->custom && slide_walls(c->q, (int)elem_bytes(c->storage));
+    if (serves && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) return {K_SLIDE, 2};
+    return {K_PUSH, 1};
+  }
   const TilePlan tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
   if (tile.steps >= 2) return {K_TILE, tile.steps};
   if (c->d == 3 && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) return {K_SLIDE, 2};
@@ -277,28 +287,26 @@ hipError_t run_tiles(const lbmrv_ctx* c, int64_t most, void* p, void* q, int64_t
   return hipSuccess;
 }
 
-// nsteps steps p -> q of a two-array form on a grid that k_slide serves: pairs
-// of steps, and as many single steps as leave an odd number of launches from
-// one array into the other (an in-place collision counts as none).
+// nsteps >= 2 steps p -> q of a two-array form on a grid that k_slide serves:
+// pairs of steps, and as many single steps as leave an odd number of launches
+// from one array into the other (an in-place collision counts as none).
 hipError_t run_pairs(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int mode, double alpha, const float* ut,
                      hipStream_t st) {
-  int64_t pairs = nsteps / 2, singles = nsteps % 2;
+  int64_t pairs = nsteps / 2;
   bool collided = false;  // the state in `cur` is post-collision
   void *cur = p, *other = q;
   hipError_t e;
-  auto push = [&]() -> hipError_t {
-    const hipError_t er = run_kind(c, K_PUSH, cur, other, mode, alpha, ut, st);
-    std::swap(cur, other);
+  auto single = [&](int kind, void* to) -> hipError_t {
+    const hipError_t er = run_kind(c, kind, cur, to, mode, alpha, ut, st);
+    if (to != cur) std::swap(cur, other);
+    collided = true;
     return er;
   };
-  if (singles == 1 && pairs % 2 == 1) {  // pairs alone end in q: collide in place first
-    if ((e = run_kind(c, K_COLLIDE, cur, cur, mode, alpha, ut, st)) != hipSuccess) return e;
-    collided = true;
-  } else if (singles == 1) {
-    if ((e = push()) != hipSuccess) return e;
+  if (nsteps % 2 == 1) {
+    if ((e = single(K_COLLIDE, pairs % 2 == 1 ? cur : other)) != hipSuccess) return e;
   } else if (pairs % 2 == 0) {  // one pair as two single steps
     --pairs;
-    if ((e = push()) != hipSuccess || (e = push()) != hipSuccess) return e;
+    if ((e = single(K_COLLIDE, other)) != hipSuccess || (e = single(K_PULL, other)) != hipSuccess) return e;
   }
   StepLaunch L = base_launch(c, st);
   L.kind = K_SLIDE;
@@ -320,9 +328,9 @@ hipError_t run_pairs(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int m
   return hipSuccess;
 }
 
-// nsteps >= 2 steps p -> q of the two-array forms without walls by the kernels
-// that take several steps per launch; false (and nothing launched) if single
-// steps are the better choice on this grid.
+// nsteps >= 2 steps p -> q of the two-array forms by the kernels that take
+// several steps per launch; false (and nothing launched) if single steps are the
+// better choice on this grid.
 bool run_fused(const lbmrv_ctx* c, void* p, void* q, int64_t nsteps, int mode, double alpha, const float* ut,
                hipStream_t st, hipError_t& e) {
   const Fused f = fused_kind(c);
@@ -848,17 +856,15 @@ int lbmrv_step(lbmrv_ctx* c, void* f_in, void* f_out, int ut_mode, double ut_alp
   }
   hipError_t e = hipSuccess;
   // Both two-array forms give the same bits and both read and write both
-  // arrays, so without walls they share the cheaper routes: one step is one
+  // arrays, so they share the cheaper routes: without walls one step is one
   // collide-and-scatter pass (the pull form's collision and transport are
   // two), and more steps go several per launch where the grid allows it.
-  if (!c->wall_mask) {
-    if (nsteps == 1) {
-      e = run_kind(c, K_PUSH, f_in, f_out, ut_mode, ut_alpha, ut_field, st);
-      return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
-    }
-    if (run_fused(c, f_in, f_out, nsteps, ut_mode, ut_alpha, ut_field, st, e))
-      return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
+  if (nsteps == 1 && !c->wall_mask) {
+    e = run_kind(c, K_PUSH, f_in, f_out, ut_mode, ut_alpha, ut_field, st);
+    return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
   }
+  if (nsteps >= 2 && run_fused(c, f_in, f_out, nsteps, ut_mode, ut_alpha, ut_field, st, e))
+    return e == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
   if (c->streaming == LBMRV_STREAM_PUSH) {
     // Pre-collision state throughout: one fused collide-and-scatter pass per
     // step.  Out-of-place passes alternate between the two buffers, so an odd

@@ -185,10 +185,16 @@ hipError_t launch_slide_t(const StepLaunch& L) {
     SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter, L.keep};
     StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
     dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.chunk - 1) / p.chunk);
-    if (L.keep)
-      hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, true>), grid, dim3(SlideShape<B, ST>::threads), 0, L.stream, a, g);
-    else
-      hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false>), grid, dim3(SlideShape<B, ST>::threads), 0, L.stream, a, g);
+    const dim3 threads(SlideShape<B, ST>::threads);
+    if (L.wall_mask) {
+      if constexpr (slide_walls(B::Q, (int)sizeof(typename Store<ST>::S)) && RLX == 0) {
+        hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false, true>), grid, threads, 0, L.stream, a, g);
+        return hipGetLastError();
+      }
+      return hipErrorInvalidValue;
+    }
+    if (L.keep) hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, true, false>), grid, threads, 0, L.stream, a, g);
+    else hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false, false>), grid, threads, 0, L.stream, a, g);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

@@ -98,9 +98,20 @@ inline SlidePlan plan_slide(int q, int eb, uint32_t nx, uint32_t ny, uint32_t nz
   return p;
 }
 
+// Whether the walled instances exist: the others have no registers left for the
+// values more (D3Q19 FP64 spills 88 of them, D3Q27 FP32 18).
+constexpr bool slide_walls(int q, int eb) { return q == 19 && eb == 4; }
+
 // KEEP: the state between the two steps is stored too (g.keep); an instance of
 // its own, as testing for it took ten registers (D3Q27 FP32 192^3: 480 -> 533 us).
-template <class B, int ST, int MODE, int RLX, bool KEEP>
+// WALLS: half-way bounce-back on both faces of the x or y axis (not z).  A value
+// whose source lies beyond a wall is the node's own opposite one of the same
+// plane: step one reads it instead of the shifted value, step two finds it in
+// the LDS copy of plane p - 1 or, for c_z > 0 (its opposite has one copy only,
+// by now plane p's), in registers kept from the previous iteration.  D3Q19 256^3
+// FP32, walls on the y faces: 703 us for two steps, 2 x 434 by single ones (592
+// without walls: the tiles along a wall are the slowest of the one round).
+template <class B, int ST, int MODE, int RLX, bool KEEP, bool WALLS>
 __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs<typename Store<ST>::T> a, SlideArgs g) {
   using L = typename B::Lat;
   using S = typename Store<ST>::S;
@@ -147,6 +158,38 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
     return Steps{x_lo ? wx : 0u - E, x_hi ? 0u - wx : E, y_lo ? wy : 0u - sy, y_hi ? 0u - wy : sy};
   };
 
+  // Walls: whether the link from x - c_j to this column's nodes passes one on
+  // the x axis, or else on the y axis, and the bounced value (as bounce() of
+  // kernels.hpp).  Both faces' terms are formed from uniform values and one is
+  // picked per lane: a load of the lane's own face would have to wait for the
+  // prefetched plane behind it (D3Q19 256^3 channel: 963 us for two steps).
+  // The mask is opaque, so that nothing formed from it stays in the registers
+  // of the plane loop.
+  auto walls_now = [&]() -> uint32_t {
+    uint32_t mask = a.wall_mask;
+    if constexpr (WALLS) asm volatile("" : "+v"(mask));
+    return mask;
+  };
+  auto wall_on = [&](auto jj, auto axis, uint32_t mask) -> bool {
+    constexpr int c = decltype(axis)::value == 0 ? L::c[jj].x : L::c[jj].y;
+    if constexpr (!WALLS || c == 0) return false;
+    else if constexpr (decltype(axis)::value == 0) return c > 0 ? x_lo && (mask & 1u) : x_hi && (mask & 2u);
+    else return c > 0 ? y_lo && (mask & 4u) : y_hi && (mask & 8u);
+  };
+  constexpr std::integral_constant<int, 0> x_axis{};
+  constexpr std::integral_constant<int, 1> y_axis{};
+  auto walled = [&](auto jj, uint32_t mask) -> bool { return wall_on(jj, x_axis, mask) || wall_on(jj, y_axis, mask); };
+  auto bounced = [&](auto jj, uint32_t mask, T reflected) -> T {
+    constexpr int J = jj;
+    constexpr int fx = L::c[J].x > 0 ? 0 : 1, fy = L::c[J].y > 0 ? 2 : 3;
+    const T via_x = bounce<B, T, J>(a.wall_coef, fx, reflected), via_y = bounce<B, T, J>(a.wall_coef, fy, reflected);
+    return wall_on(jj, x_axis, mask) ? via_x : via_y;
+  };
+  // whether any column of this wavefront lies at a wall: the others take the
+  // plain code
+  const bool at_wall = WALLS && __any((x_lo && (a.wall_mask & 1u)) || (x_hi && (a.wall_mask & 2u)) ||
+                                      (y_lo && (a.wall_mask & 4u)) || (y_hi && (a.wall_mask & 8u)));
+
   auto load = [&](int p, T (&h)[Q], T (&u)[3]) {
     const int z = wrapz(p), zm = wrapz(z - 1), zp = wrapz(z + 1);
     const uint64_t bz = (uint64_t)z * plane, bm = (uint64_t)zm * plane, bp = (uint64_t)zp * plane;
@@ -155,13 +198,23 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
     const char* pop = static_cast<const char*>(a.fin);
     if (g.gather) {
       const Steps d = steps_of();
-      sfor<Q>([&](auto jj) {
-        constexpr int cx = L::c[jj].x, cy = L::c[jj].y, cz = L::c[jj].z;
-        uint32_t n = at + (cy > 0 ? d.ym : cy < 0 ? d.yp : 0u) + (cx > 0 ? d.xm : cx < 0 ? d.xp : 0u);
-        asm volatile("" : "+v"(n));
-        h[jj] = T(*reinterpret_cast<const S*>(pop + E * (cz > 0 ? bm : cz < 0 ? bp : bz) + n));
-        pop += stride;
-      });
+      auto gather = [&](auto near) {
+        const uint32_t mask = walls_now();
+        sfor<Q>([&](auto jj) {
+          constexpr int cx = L::c[jj].x, cy = L::c[jj].y, cz = L::c[jj].z;
+          uint32_t n = at + (cy > 0 ? d.ym : cy < 0 ? d.yp : 0u) + (cx > 0 ? d.xm : cx < 0 ? d.xp : 0u);
+          asm volatile("" : "+v"(n));
+          const char* from = pop + E * (cz > 0 ? bm : cz < 0 ? bp : bz) + n;
+          if constexpr (decltype(near)::value) {
+            if (walled(jj, mask))  // the moving wall's term is added where the value is used
+              from = static_cast<const char*>(a.fin) + (uint64_t)opposite<L>(jj) * stride + E * bz + at;
+          }
+          h[jj] = T(*reinterpret_cast<const S*>(from));
+          pop += stride;
+        });
+      };
+      if (at_wall) gather(std::true_type{});
+      else gather(std::false_type{});
     } else {
       uint32_t n = at;
       asm volatile("" : "+v"(n));
@@ -178,6 +231,7 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
 
   T hn[Q], un[3] = {T(0), T(0), T(0)}, up[3] = {T(0), T(0), T(0)};  // next plane; u~ of the previous one
   S c0 = S(0), cu1 = S(0), cu2 = S(0), cd = S(0);  // own column: rest, +z of the last two planes, -z
+  S own_dn[Q];  // WALLS: this column's values with c_z < 0 of the previous plane
   load(z0 - 1, hn, un);
   int k = 0, k3 = 0;  // planes so far, and modulo 3
   for (int p = z0 - 1; p <= z1; ++p) {
@@ -186,6 +240,14 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
     T h[Q], uc[3] = {T(0), T(0), T(0)};
     sfor<Q>([&](auto jj) { h[jj] = hn[jj]; });
     sfor<3>([&](auto al) { uc[al] = un[al]; });
+    if constexpr (WALLS) {
+      if (at_wall && g.gather) {
+        const uint32_t mask = walls_now();
+        sfor<Q>([&](auto jj) {
+          h[jj] = walled(jj, mask) ? bounced(jj, mask, h[jj]) : h[jj];
+        });
+      }
+    }
     collide_node<B, T, MODE, RLX>(h, a, uc);
     S o[Q];
     sfor<Q>([&](auto jj) { o[jj] = S(h[jj]); });
@@ -217,6 +279,25 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
           h[J] = T(lf[SL::base(J) * R - L::c[J].y * PX - L::c[J].x + (L::c[J].z < 0 ? 0 : L::c[J].z == 0 ? r0 : ru) + tid]);
         }
       });
+      if constexpr (WALLS) {
+        if (at_wall) {
+          const uint32_t mask = walls_now();
+          sfor<Q>([&](auto jj) {
+            constexpr int J = jj, O = opposite<L>(J);
+            if constexpr (!SL::axis(J)) {
+              const S back = L::c[J].z > 0
+                                 ? own_dn[O]
+                                 : lf[SL::base(O) * R + (L::c[J].z == 0 ? r0 : (k3 == 0 ? 2 : k3 - 1) * R) + tid];
+              h[J] = walled(jj, mask) ? bounced(jj, mask, T(back)) : h[J];
+            }
+          });
+        }
+      }
+    }
+    if constexpr (WALLS) {
+      sfor<Q>([&](auto jj) {
+        if constexpr (L::c[jj].z < 0 && !SL::axis(jj)) own_dn[jj] = o[jj];
+      });
     }
     __syncthreads();
     if (p > z0 && owned) {
@@ -240,11 +321,17 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
       char* pop = static_cast<char*>(a.fout);
       if (g.scatter) {
         const Steps d = steps_of();
+        const uint32_t mask = walls_now();
         sfor<Q>([&](auto jj) {
           constexpr int cx = L::c[jj].x, cy = L::c[jj].y, cz = L::c[jj].z;
           uint32_t n = at + (cy < 0 ? d.ym : cy > 0 ? d.yp : 0u) + (cx < 0 ? d.xm : cx > 0 ? d.xp : 0u);
           asm volatile("" : "+v"(n));
-          *reinterpret_cast<S*>(pop + E * (cz < 0 ? bm : cz > 0 ? bp : bz) + n) = o[jj];
+          constexpr int O = opposite<L>(jj);
+          constexpr std::integral_constant<int, O> oo{};
+          if (walled(oo, mask))  // the destination lies beyond a wall: back to this node
+            *reinterpret_cast<S*>(static_cast<char*>(a.fout) + (uint64_t)O * stride + E * bz + at) =
+                S(bounced(oo, mask, T(o[jj])));
+          else *reinterpret_cast<S*>(pop + E * (cz < 0 ? bm : cz > 0 ? bp : bz) + n) = o[jj];
           pop += stride;
         });
       } else {

@@ -171,3 +171,26 @@ def test_small_grids_in_one_workgroup(lattice, shape, storage):
 
 def test_more_steps_than_one_launch_takes():
     compare("d2q9", (3, 5), "f64", "fluid", (4096, 4097), streaming=("pull",))
+
+
+# walls on both faces of an axis (moving ones among them); a wall on one face, a z
+# wall and other storages keep single steps
+@pytest.mark.parametrize("lattice,shape", [("d3q19", (70, 64, 64)), ("d3q19", (16, 97, 257)), ("d3q27", (80, 80, 81))])
+@pytest.mark.parametrize("mask", [0b1100, 0b0100, 0b1111, 0b0010, 0b101100])
+def test_pairs_with_walls_equal_single_steps(lattice, shape, mask):
+    lat = oracle_lattice(lattice)
+    storage = "f32dev" if mask & 1 else "f32"
+    st, _ = to_storage(lat, far_state(lat, shape, seed=45, amp=0.02, umax=0.05), storage)
+    f0 = torch.from_numpy(st).cuda()
+    ctx = Lbmrv(lattice, RATES[lattice], tuple(reversed(shape)), storage)
+    ctx.set_walls(mask, [[0.0, 0.03, 0.0], [0.0, 0.0, 0.01], [0.02, 0.0, 0.0], [0.05, 0.0, 0.01]] + [[0.0] * 3] * 2, 1.1)
+    f = f0.clone()
+    for n in range(1, 7):
+        g = torch.empty_like(f)
+        ctx.collide(f, g, "fluid", 0.7)
+        ctx.transport(g, f)
+        if n in (2, 3, 5, 6):
+            a, b = f0.clone(), torch.full_like(f0, float("nan"))
+            ctx.step(a, b, "fluid", 0.7, None, n)
+            torch.cuda.synchronize()
+            assert torch.equal(b, f), n

@@ -18,15 +18,11 @@
 
 namespace lbmrv {
 
-// Totals of the kRedBlocks rows of five partial sums, in a fixed order:
-// out[0] = sum + add0, out[1 + a] = scale * sum (a < d, else 0), out[4] = the
-// count of non-finite values.
-__global__ __launch_bounds__(kRedThreads) void k_conserve_final(const double* partial, double* out, double add0,
-                                                                double scale, int d) {
+__global__ __launch_bounds__(kRedThreads) void k_conserve_final(RedOut o, int rows) {
   __shared__ double red[5][kRedThreads];
   double acc[5] = {0, 0, 0, 0, 0};
-  for (int b = threadIdx.x; b < kRedBlocks; b += kRedThreads)
-    for (int i = 0; i < 5; ++i) acc[i] += partial[(uint64_t)b * 5 + i];
+  for (int b = threadIdx.x; b < rows; b += kRedThreads)
+    for (int i = 0; i < 5; ++i) acc[i] += o.partial[(uint64_t)b * 5 + i];
   for (int i = 0; i < 5; ++i) red[i][threadIdx.x] = acc[i];
   __syncthreads();
   for (int w = kRedThreads / 2; w > 0; w >>= 1) {
@@ -34,9 +30,10 @@ __global__ __launch_bounds__(kRedThreads) void k_conserve_final(const double* pa
       for (int i = 0; i < 5; ++i) red[i][threadIdx.x] += red[i][threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0][0] + add0;
-  if (threadIdx.x >= 1 && threadIdx.x <= 3) out[threadIdx.x] = (int)threadIdx.x <= d ? scale * red[threadIdx.x][0] : 0.0;
-  if (threadIdx.x == 4) out[4] = red[4][0];
+  if (threadIdx.x == 0) o.out[0] = red[0][0] + o.add0;
+  if (threadIdx.x >= 1 && threadIdx.x <= 3)
+    o.out[threadIdx.x] = (int)threadIdx.x <= o.d ? o.scale * red[threadIdx.x][0] : 0.0;
+  if (threadIdx.x == 4) o.out[4] = red[4][0];
 }
 
 __global__ __launch_bounds__(256) void k_fill_zero(double* p, uint64_t n) {
@@ -76,10 +73,10 @@ using PlanFn = TilePlan (*)(uint32_t, uint32_t, uint32_t);
 using AdjFn = hipError_t (*)(const AdjLaunch&);
 using FinFn = hipError_t (*)(void*, uint32_t, uint32_t, uint32_t, uint64_t, const FinArgs&, hipStream_t);
 using MomFn = hipError_t (*)(const MomLaunch&);
-using ConsFn = hipError_t (*)(const void*, uint64_t, double*, hipStream_t);
+using ConsFn = hipError_t (*)(const void*, uint64_t, const RedOut&, hipStream_t);
 using InitFn = hipError_t (*)(const InitLaunch&);
 using ConvFn = hipError_t (*)(const void*, void*, double, uint64_t, int, hipStream_t);
-using DevNormFn = hipError_t (*)(const void*, uint64_t, const DevRef&, double*, hipStream_t);
+using DevNormFn = hipError_t (*)(const void*, uint64_t, const DevRef&, const RedOut&, hipStream_t);
 using DevScaleFn = hipError_t (*)(void*, uint64_t, const DevRef&, double, hipStream_t);
 
 struct Entry {
@@ -131,7 +128,8 @@ struct lbmrv_ctx {
   uint32_t nx, ny, nz;
   uint64_t N;
   double rho0;    // 0 unless a deviation storage
-  double* partial = nullptr;  // kRedBlocks * 5 partial sums + 5 results (device)
+  double* partial = nullptr;  // kRedBlocks rows of 5 partial sums (device)
+  double* totals = nullptr;   // 5 totals (host memory the GPU writes)
   int partial_dev = -1;
   uint32_t wall_mask = 0;     // half-way bounce-back faces (bit 2a + side)
   double wall_u[6][3] = {};   // wall velocities (physical units)
@@ -949,28 +947,39 @@ int lbmrv_moments(lbmrv_ctx* c, const void* f, void* rho, void* u, void* m0, voi
   return kEntries[c->entry].mom[c->sk](L) == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
 }
 
-// Runs a partial-sum kernel over the context's reduction buffer (allocated on
-// the first call, on the current device), sums its kRedBlocks rows in a fixed
-// order (the total of slot 0 plus add0, slots 1..d times scale) and copies the
-// five totals to the host; blocking on `st`.
+// Launches the kernels of one reduction.
+extern "C++" template <class Partial>
+static hipError_t launch_reduction(const lbmrv_ctx* c, Partial partial, const RedOut& o, hipStream_t st) {
+  hipError_t e = partial(o);
+  const unsigned rows = red_rows(c->N);
+  if (e != hipSuccess || rows == 1) return e;
+  hipLaunchKernelGGL(k_conserve_final, dim3(1), dim3(kRedThreads), 0, st, o, (int)rows);
+  return hipGetLastError();
+}
+
+// Runs a reduction over the context's buffers (allocated on the first call, on
+// the current device) and returns the five totals: slot 0 plus add0, slots 1..d
+// times scale, and the count; blocking on `st`.  The GPU writes the totals into
+// host memory, which saves the copy that would otherwise follow.
 extern "C++" template <class Partial>
 static int reduce5(lbmrv_ctx* c, Partial partial, double add0, double scale, hipStream_t st, double (&h)[5]) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return LBMRV_ERR_HIP;
   if (c->partial && c->partial_dev != dev) return LBMRV_ERR_INVALID_ARG;  // context bound to its first device
   if (!c->partial) {
-    if (hipMalloc(&c->partial, sizeof(double) * (kRedBlocks * 5 + 8)) != hipSuccess) {
+    if (!c->totals && hipHostMalloc(reinterpret_cast<void**>(&c->totals), sizeof(double) * 5) != hipSuccess) {
+      c->totals = nullptr;
+      return LBMRV_ERR_HIP;
+    }
+    if (hipMalloc(&c->partial, sizeof(double) * kRedBlocks * 5) != hipSuccess) {
       c->partial = nullptr;
       return LBMRV_ERR_HIP;
     }
     c->partial_dev = dev;
   }
-  if (partial(c->partial) != hipSuccess) return LBMRV_ERR_HIP;
-  double* res = c->partial + kRedBlocks * 5;
-  hipLaunchKernelGGL(k_conserve_final, dim3(1), dim3(kRedThreads), 0, st, c->partial, res, add0, scale, c->d);
-  if (hipGetLastError() != hipSuccess) return LBMRV_ERR_HIP;
-  if (hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return LBMRV_ERR_HIP;
+  if (launch_reduction(c, partial, RedOut{c->partial, c->totals, add0, scale, c->d}, st) != hipSuccess) return LBMRV_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return LBMRV_ERR_HIP;
+  for (int i = 0; i < 5; ++i) h[i] = c->totals[i];
   return LBMRV_OK;
 }
 
@@ -984,7 +993,7 @@ int lbmrv_conservation(lbmrv_ctx* c, const void* f, double out[4], void* hip_str
   if ((rc = check_ptr(f, elem_bytes(c->storage)))) return rc;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   double h[5];
-  if ((rc = reduce5(c, [&](double* p) { return kEntries[c->entry].cons[c->sk](f, c->N, p, st); }, conserve_add0(c),
+  if ((rc = reduce5(c, [&](const RedOut& o) { return kEntries[c->entry].cons[c->sk](f, c->N, o, st); }, conserve_add0(c),
                     c->lambda, st, h)))
     return rc;
   for (int i = 0; i < 4; ++i) out[i] = h[i];
@@ -1022,12 +1031,13 @@ int lbmrv_conservation_noalloc(lbmrv_ctx* c, const void* f, double* out_dev, voi
   double* part = nullptr;
   if ((rc = scratch_for_current_device(&part))) return rc;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  // the partial kernel writes every row of the scratch before the final
-  // kernel reads it, so nothing needs clearing between calls
-  if (kEntries[c->entry].cons[c->sk](f, c->N, part, st) != hipSuccess) return LBMRV_ERR_HIP;
-  hipLaunchKernelGGL(k_conserve_final, dim3(1), dim3(kRedThreads), 0, st, part, out_dev, conserve_add0(c), c->lambda,
-                     c->d);
-  return hipGetLastError() == hipSuccess ? LBMRV_OK : LBMRV_ERR_HIP;
+  // every row of the scratch that is read has been written before, so nothing
+  // needs clearing between calls
+  const RedOut o{part, out_dev, conserve_add0(c), c->lambda, c->d};
+  return launch_reduction(c, [&](const RedOut& r) { return kEntries[c->entry].cons[c->sk](f, c->N, r, st); }, o, st) ==
+                 hipSuccess
+             ? LBMRV_OK
+             : LBMRV_ERR_HIP;
 }
 
 // The reference populations in the stored representation; INVALID_ARG if
@@ -1051,7 +1061,7 @@ int lbmrv_deviation_norm(lbmrv_ctx* c, const void* f, const double* f_ref, doubl
   if ((rc = check_ptr(f, elem_bytes(c->storage))) || (rc = dev_ref(c, f_ref, r))) return rc;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   double h[5];
-  if ((rc = reduce5(c, [&](double* p) { return kEntries[c->entry].dnorm[c->sk](f, c->N, r, p, st); }, 0.0, 1.0,
+  if ((rc = reduce5(c, [&](const RedOut& o) { return kEntries[c->entry].dnorm[c->sk](f, c->N, r, o, st); }, 0.0, 1.0,
                     st, h)))
     return rc;
   out[0] = h[0];
@@ -1354,6 +1364,7 @@ void lbmrv_destroy(lbmrv_ctx* c) {
   for (auto& ev : c->aev)
     if (ev) (void)hipEventDestroy(ev);
   if (c->partial) (void)hipFree(c->partial);
+  if (c->totals) (void)hipHostFree(c->totals);
   if (c->dtab) (void)hipFree(c->dtab);
   delete c;
 }

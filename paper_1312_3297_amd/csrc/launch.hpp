@@ -276,14 +276,14 @@ hipError_t launch_moments_t(const MomLaunch& L) {
 }
 
 template <class B, int ST>
-hipError_t launch_conserve_partial(const void* f, uint64_t N, double* partial, hipStream_t st) {
-  hipLaunchKernelGGL((k_conserve_partial<B, ST>), dim3(kRedBlocks), dim3(kRedThreads), 0, st, f, N, partial);
+hipError_t launch_conserve_partial(const void* f, uint64_t N, const RedOut& o, hipStream_t st) {
+  hipLaunchKernelGGL((k_conserve_partial<B, ST>), dim3(red_rows(N)), dim3(kRedThreads), 0, st, f, N, o);
   return hipGetLastError();
 }
 
 template <class B, int ST>
-hipError_t launch_devnorm_t(const void* f, uint64_t N, const DevRef& ref, double* partial, hipStream_t st) {
-  hipLaunchKernelGGL((k_dev_partial<B, ST>), dim3(kRedBlocks), dim3(kRedThreads), 0, st, f, N, ref, partial);
+hipError_t launch_devnorm_t(const void* f, uint64_t N, const DevRef& ref, const RedOut& o, hipStream_t st) {
+  hipLaunchKernelGGL((k_dev_partial<B, ST>), dim3(red_rows(N)), dim3(kRedThreads), 0, st, f, N, ref, o);
   return hipGetLastError();
 }
 
@@ -440,7 +440,7 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
   hipError_t launch_step_##NAME##_##SKN(const StepLaunch& L);                               \
   TilePlan plan_tile_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz);                 \
   hipError_t launch_moments_##NAME##_##SKN(const MomLaunch& L);                             \
-  hipError_t launch_conserve_##NAME##_##SKN(const void* f, uint64_t N, double* partial,     \
+  hipError_t launch_conserve_##NAME##_##SKN(const void* f, uint64_t N, const RedOut& o,     \
                                             hipStream_t st);                                \
   hipError_t launch_init_##NAME##_##SKN(const InitLaunch& L);                               \
   hipError_t launch_adjoint_##NAME##_##SKN(const AdjLaunch& L);                             \
@@ -450,7 +450,7 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
   hipError_t launch_convert_##NAME##_##SKN(const void* in, void* out, double rho0, uint64_t N, \
                                            int to_storage, hipStream_t st);                  \
   hipError_t launch_devnorm_##NAME##_##SKN(const void* f, uint64_t N, const DevRef& ref,    \
-                                           double* partial, hipStream_t st);                \
+                                           const RedOut& o, hipStream_t st);                \
   hipError_t launch_devscale_##NAME##_##SKN(void* f, uint64_t N, const DevRef& ref, double factor, \
                                             hipStream_t st);
 
@@ -462,9 +462,9 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
   hipError_t launch_moments_##NAME##_##SKN(const MomLaunch& L) {                            \
     return launch_moments_t<BASIS, ST>(L);                                                  \
   }                                                                                         \
-  hipError_t launch_conserve_##NAME##_##SKN(const void* f, uint64_t N, double* partial,     \
+  hipError_t launch_conserve_##NAME##_##SKN(const void* f, uint64_t N, const RedOut& o,     \
                                             hipStream_t st) {                               \
-    return launch_conserve_partial<BASIS, ST>(f, N, partial, st);                           \
+    return launch_conserve_partial<BASIS, ST>(f, N, o, st);                                 \
   }                                                                                         \
   hipError_t launch_init_##NAME##_##SKN(const InitLaunch& L) { return launch_init_t<BASIS, ST>(L); } \
   hipError_t launch_adjoint_##NAME##_##SKN(const AdjLaunch& L) { return launch_adjoint_s<BASIS, ST>(L); } \
@@ -478,8 +478,8 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
     return launch_convert_t<BASIS, ST>(in, out, rho0, N, to_storage, st);                   \
   }                                                                                         \
   hipError_t launch_devnorm_##NAME##_##SKN(const void* f, uint64_t N, const DevRef& ref,    \
-                                           double* partial, hipStream_t st) {               \
-    return launch_devnorm_t<BASIS, ST>(f, N, ref, partial, st);                             \
+                                           const RedOut& o, hipStream_t st) {               \
+    return launch_devnorm_t<BASIS, ST>(f, N, ref, o, st);                                   \
   }                                                                                         \
   hipError_t launch_devscale_##NAME##_##SKN(void* f, uint64_t N, const DevRef& ref, double factor, \
                                             hipStream_t st) {                               \

@@ -194,3 +194,30 @@ def test_pairs_with_walls_equal_single_steps(lattice, shape, mask):
             ctx.step(a, b, "fluid", 0.7, None, n)
             torch.cuda.synchronize()
             assert torch.equal(b, f), n
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (32, 64), (3, 683), (257, 255), (513, 512)])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
+def test_sums_at_the_edges_of_their_rows(shape, storage):
+    """One workgroup up to 2048 nodes, a row per 256 nodes, 1024 rows at most.
+    Each sum is a chain of at most some 600 FP64 additions of terms up to
+    |f|: 1e-13 of the sum of magnitudes."""
+    lat = oracle_lattice("d2q9")
+    st, f64 = to_storage(lat, far_state(lat, shape, seed=47, amp=0.02, umax=0.05), storage)
+    f = torch.from_numpy(st).cuda()
+    ctx = Lbmrv("d2q9", RATES["d2q9"], tuple(reversed(shape)), storage)
+    mass, mom, finite = ctx.conservation(f)
+    tol = 1e-13 * np.abs(f64).sum()
+    assert finite and abs(mass - f64.sum()) <= tol
+    for a in range(2):
+        assert abs(mom[a] - np.tensordot(lat.c[:, a].astype(float), f64, axes=(0, 0)).sum()) <= tol
+    ref = np.linspace(0.1, 0.2, 9)
+    d2 = ((f64 - ref.reshape(9, 1, 1)) ** 2).sum()
+    norm2, finite = ctx.deviation_norm2(f, ref)
+    assert finite and abs(norm2 - d2) <= 1e-12 * d2   # the stored reference is rounded once more
+    out = torch.zeros(5, dtype=torch.float64, device="cuda")
+    flat = f.view(-1)
+    flat[0], flat[-1] = float("inf"), float("nan")
+    ctx.conservation_noalloc(f, out)
+    assert out[4].item() == 2.0
+    assert not ctx.conservation(f)[2] and not ctx.deviation_norm2(f, ref)[1]

@@ -70,6 +70,7 @@ namespace {
 
 using StepFn = hipError_t (*)(const StepLaunch&);
 using PlanFn = TilePlan (*)(uint32_t, uint32_t, uint32_t);
+using SlidePlanFn = SlidePlan (*)(uint32_t, uint32_t, uint32_t);
 using AdjFn = hipError_t (*)(const AdjLaunch&);
 using FinFn = hipError_t (*)(void*, uint32_t, uint32_t, uint32_t, uint64_t, const FinArgs&, hipStream_t);
 using MomFn = hipError_t (*)(const MomLaunch&);
@@ -82,6 +83,7 @@ using DevScaleFn = hipError_t (*)(void*, uint64_t, const DevRef&, double, hipStr
 struct Entry {
   StepFn step[3];
   PlanFn tile[3];
+  SlidePlanFn slide[3];
   MomFn mom[3];
   ConsFn cons[3];
   InitFn init[3];
@@ -97,6 +99,7 @@ struct Entry {
   Entry {                                                                                 \
     {launch_step_##NAME##_f64, launch_step_##NAME##_f32, launch_step_##NAME##_f16},       \
         {plan_tile_##NAME##_f64, plan_tile_##NAME##_f32, plan_tile_##NAME##_f16},         \
+        {plan_slide_##NAME##_f64, plan_slide_##NAME##_f32, plan_slide_##NAME##_f16},      \
         {launch_moments_##NAME##_f64, launch_moments_##NAME##_f32, launch_moments_##NAME##_f16}, \
         {launch_conserve_##NAME##_f64, launch_conserve_##NAME##_f32, launch_conserve_##NAME##_f16}, \
         {launch_init_##NAME##_f64, launch_init_##NAME##_f32, launch_init_##NAME##_f16},   \
@@ -244,20 +247,19 @@ struct Fused {
   int64_t steps;
 };
 Fused fused_kind(const lbmrv_ctx* c) {
+  const bool slides = kEntries[c->entry].slide[c->sk](c->nx, c->ny, c->nz).chunk != 0;
   if (c->wall_mask) {
     // k_slide has walls on x and y faces, for the built-in bases; on both faces of
     // an axis, as its last launch scatters (past a single wall, the slot a node
     // bounces into would also be reached through the open face)
     const uint32_t m = c->wall_mask;
     const bool paired = (m & 1u) == ((m >> 1) & 1u) && ((m >> 2) & 1u) == ((m >> 3) & 1u);
-    const bool serves = c->d == 3 && !(m >> 4) && paired && !c->custom && slide_walls(c->q, (int)elem_bytes(c->storage));
-    if (serves && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) return {K_SLIDE, 2};
+    if (slides && !(m >> 4) && paired && !c->custom && slide_walls(c->q, (int)elem_bytes(c->storage))) return {K_SLIDE, 2};
     return {K_PUSH, 1};
   }
   const TilePlan tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
   if (tile.steps >= 2) return {K_TILE, tile.steps};
-  if (c->d == 3 && plan_slide(c->q, (int)elem_bytes(c->storage), c->nx, c->ny, c->nz).chunk) return {K_SLIDE, 2};
-  return {K_PUSH, 1};
+  return slides ? Fused{K_SLIDE, 2} : Fused{K_PUSH, 1};
 }
 
 // nsteps steps p -> q of a two-array form on a grid that k_tile serves (`most`

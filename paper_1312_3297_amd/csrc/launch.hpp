@@ -180,12 +180,12 @@ hipError_t launch_tile_t(const StepLaunch& L) {
 template <class B, int ST, int MODE, int RLX>
 hipError_t launch_slide_t(const StepLaunch& L) {
   if constexpr (B::Lat::D == 3 && ST != 2) {
-    const SlidePlan p = plan_slide(B::Q, sizeof(typename Store<ST>::S), L.nx, L.ny, L.nz);
+    const SlidePlan p = plan_slide<B, ST>(L.nx, L.ny, L.nz);
     if (!p.chunk) return hipErrorInvalidValue;
     SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter, L.keep};
     StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
     dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.chunk - 1) / p.chunk);
-    const dim3 threads(SlideShape<B, ST>::threads);
+    const dim3 threads(p.threads);
     if (L.wall_mask) {
       if constexpr (slide_walls(B::Q, (int)sizeof(typename Store<ST>::S)) && RLX == 0) {
         hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false, true>), grid, threads, 0, L.stream, a, g);
@@ -439,6 +439,7 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
 #define LBMRV_DECLARE_LAUNCHERS(NAME, SKN)                                                  \
   hipError_t launch_step_##NAME##_##SKN(const StepLaunch& L);                               \
   TilePlan plan_tile_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz);                 \
+  SlidePlan plan_slide_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz);               \
   hipError_t launch_moments_##NAME##_##SKN(const MomLaunch& L);                             \
   hipError_t launch_conserve_##NAME##_##SKN(const void* f, uint64_t N, const RedOut& o,     \
                                             hipStream_t st);                                \
@@ -458,6 +459,10 @@ constexpr bool has_adjoint2(int d, int sk) { return d == 2 && sk != SK_F64; }
   hipError_t launch_step_##NAME##_##SKN(const StepLaunch& L) { return launch_step_s<BASIS, ST>(L); } \
   TilePlan plan_tile_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz) {                \
     return plan_tile<BASIS, ST>(nx, ny, nz);                                                \
+  }                                                                                         \
+  SlidePlan plan_slide_##NAME##_##SKN(uint32_t nx, uint32_t ny, uint32_t nz) {              \
+    if constexpr (BASIS::Lat::D == 3) return plan_slide<BASIS, ST>(nx, ny, nz);             \
+    else return SlidePlan{};                                                                \
   }                                                                                         \
   hipError_t launch_moments_##NAME##_##SKN(const MomLaunch& L) {                            \
     return launch_moments_t<BASIS, ST>(L);                                                  \

@@ -15,9 +15,9 @@
 // fell out of L2 before the neighbouring tile took them (D3Q19 256^3: 1.73 GB
 // read for 1.28 GB, 592 us for two steps against 2 x 429).  Loading the next
 // plane after the first collision instead of before it keeps fewer lines in
-// flight and measured 592 against 665 us; 34 x 15 columns (two workgroups per
-// CU) 617, 66 x 15 and 34 x 30 (1024 threads) 660, a third LDS copy that saves
-// one of the two barriers 593, non-temporal stores 601 us.
+// flight and measured 592 against 665 us; 66 x 15 and 34 x 30 columns (1024
+// threads) 660, a third LDS copy that saves one of the two barriers 593,
+// non-temporal stores 601 us.
 #pragma once
 
 #include "kernels.hpp"
@@ -32,14 +32,14 @@ struct SlideArgs {
   void* keep;        // KEEP: where the state between the two steps goes
 };
 
-// Columns of a workgroup, ring included.  34 x 18: whole 128-byte lines of an
-// FP32 row and 16 rows (84 % of the threads own a column), 78 KB of LDS for
-// D3Q19 FP32, 157 KB for FP64, 118 KB for D3Q27 FP32.  D3Q27 FP64 has room for
-// 26 x 16.
+// Most columns of a workgroup, ring included.  34 wide: whole 128-byte lines of
+// an FP32 row.  22 rows are 96 KB of LDS for D3Q19 FP32 and 144 KB for D3Q27
+// FP32; D3Q19 FP64 has room for 18 (157 KB), D3Q27 FP64 for 26 x 16 (160 KB).
+// plan_slide picks the rows.
 template <class B, int ST>
 struct SlideShape {
   static constexpr bool small = B::Q == 27 && ST == 0;
-  static constexpr int PX = small ? 26 : 34, PY = small ? 16 : 18;
+  static constexpr int PX = small ? 26 : 34, PY = small ? 16 : ST == 0 ? 18 : 22;
   static constexpr int threads = (PX * PY + 63) / 64 * 64;
 };
 
@@ -60,40 +60,49 @@ struct SlideSlots {
 struct SlidePlan {
   uint32_t t[2];
   uint32_t chunk;  // 0: single steps are the better choice
+  uint32_t threads;
 };
 
-// q populations of eb bytes.  FP16 storage keeps single steps: half the bytes
-// leave it bound by the vector ALU, and the ring adds to that (D3Q19 256^3:
-// 286 against 250 us per step).
-inline SlidePlan plan_slide(int q, int eb, uint32_t nx, uint32_t ny, uint32_t nz) {
+// FP16 storage keeps single steps: half the bytes leave it bound by the vector
+// ALU, and the ring adds to that (D3Q19 256^3: 286 against 250 us per step).
+template <class B, int ST>
+SlidePlan plan_slide(uint32_t nx, uint32_t ny, uint32_t nz) {
+  using Sh = SlideShape<B, ST>;
   SlidePlan p{};
   const uint64_t n = (uint64_t)nx * ny * nz;
   // Small grids have too few columns: each workgroup gets two or three planes
   // and computes four or five.  Measured, us per step, single | two per launch:
   // D3Q19 FP32 64^3 9.0 | 7.9 (k_tile: 7.0), 96^3 28.1 | 16.4; FP64 64^3 17.8 |
   // 12.9, 96^3 53.8 | 29.9; D3Q27 FP32 64^3 10.7 | 11.6, 96^3 41.2 | 26.8.
-  if (eb == 2 || n < (q == 27 ? 500000u : 1u << 17) || nz < 4) return p;
-  if ((uint64_t)nx * ny * eb >= 1ull << 32) return p;  // 32-bit byte offsets in a plane
-  const uint32_t sx = q == 27 && eb == 8 ? 24u : 32u, sy = q == 27 && eb == 8 ? 14u : 16u;
-  const uint32_t cx = (nx + sx - 1) / sx, cy = (ny + sy - 1) / sy;
-  p.t[0] = (nx + cx - 1) / cx;
-  p.t[1] = (ny + cy - 1) / cy;
-  if (p.t[0] + 1 > nx || p.t[1] + 1 > ny) return p;  // a coordinate wraps at most once
-  // grids whose extents leave more than a quarter of the columns idle
-  const uint64_t tiles = (uint64_t)cx * cy;
-  if ((uint64_t)nx * ny * 4 < tiles * sx * sy * 3) return p;
-  // chunks: a workgroup of c planes takes c + 2 iterations (and about one to
-  // start), 256 workgroups run at a time
+  if (ST == 2 || n < (B::Q == 27 ? 500000u : 1u << 17) || nz < 4) return p;
+  if ((uint64_t)nx * ny * sizeof(typename Store<ST>::S) >= 1ull << 32) return p;  // 32-bit byte offsets in a plane
+  constexpr uint32_t sx = Sh::PX - 2;
+  const uint32_t cx = (nx + sx - 1) / sx, tx = (nx + cx - 1) / cx;
+  if (tx + 1 > nx || nx * 4 < cx * sx * 3) return p;  // a coordinate wraps at most once; too many idle columns
+  // Rows and chunks: 256 workgroups run at a time, one of c planes takes c + 2
+  // iterations and about one to start, and an iteration takes a time in
+  // proportion to the wavefronts of the workgroup; in FP64 ten of them, three on
+  // two of the SIMDs, take a little more.  (D3Q27 FP32 192^3: 20 rows 467, 16
+  // rows 493, 13 rows 517 us for two steps; 201 x 117 x 83: 158, 177, 154; D3Q19
+  // FP64 256^3: - , 1154, 1221; 201 x 117 x 83: - , 177, 145.)
+  constexpr uint32_t rows[4] = {Sh::PY - 2, 16, 13, 0};
   uint64_t best = ~0ull;
-  for (uint32_t c = 1; c <= nz; ++c) {
-    const uint32_t chunk = (nz + c - 1) / c;
-    const uint64_t groups = tiles * ((nz + chunk - 1) / chunk);
-    const uint64_t cost = (groups + 255) / 256 * (chunk + 3);
-    if (cost < best) {
-      best = cost;
-      p.chunk = chunk;
+  for (uint32_t sy : rows) {
+    if (sy == 0 || sy > (uint32_t)Sh::PY - 2) continue;
+    const uint32_t cy = (ny + sy - 1) / sy, ty = (ny + cy - 1) / cy;
+    if (ty + 1 > ny || ty * 4 < sy * 3) continue;
+    const uint32_t waves = (Sh::PX * (ty + 2) + 63) / 64;
+    const uint32_t weight = 2 * waves + (ST == 0 && waves % 4 == 2);
+    for (uint32_t c = 1; c <= nz; ++c) {
+      const uint32_t chunk = (nz + c - 1) / c;
+      const uint64_t groups = (uint64_t)cx * cy * ((nz + chunk - 1) / chunk);
+      const uint64_t cost = (groups + 255) / 256 * (chunk + 3) * weight;
+      if (cost < best) {
+        best = cost;
+        p = {{tx, ty}, chunk, waves * 64};
+      }
+      if (groups > 4096) break;
     }
-    if (groups > 4096) break;
   }
   return p;
 }

@@ -93,10 +93,10 @@ def test_tiles_in_space_equal_single_steps(lattice, storage, shape):
 
 
 # two steps per launch on 3-D grids: chunks of one plane count and with a short
-# last one, tiles that divide an extent and that leave a remainder, few planes;
-# the last of each list is below the bound on idle columns (single steps)
-PAIRS = {"d3q19": [(70, 64, 64), (5, 161, 193), (131, 31, 64), (16, 97, 128), (301, 17, 33)],
-         "d3q27": [(80, 80, 81), (101, 77, 66), (7, 305, 257), (900, 24, 28)]}
+# last one, tiles of each number of rows (FP32: 20 with 257 rows), tiles that
+# divide an extent and that leave a remainder, few planes; the last of each list is below the bound on idle columns (single steps)
+PAIRS = {"d3q19": [(70, 64, 64), (5, 161, 193), (131, 31, 64), (16, 97, 128), (8, 257, 250), (301, 17, 33)],
+         "d3q27": [(80, 80, 81), (101, 77, 66), (7, 305, 257), (8, 257, 250), (900, 24, 28)]}
 
 
 @pytest.mark.parametrize("lattice", ["d3q19", "d3q27"])

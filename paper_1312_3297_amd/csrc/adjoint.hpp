@@ -39,10 +39,12 @@ struct AdjArgs {
   const T* rnninv;  // and its inverse
   uint32_t xcd_remap;  // block order, as for the step kernels (block_tile)
   uint32_t eq_maxwell; // 1: equilibrium moments of the continuous Maxwellian
-  uint32_t rnx, rny;   // k_adjoint: floor(2^32 / nx) and floor(2^32 / ny), at most 2^32 - 1
+  uint32_t rnx, rny;   // floor(2^32 / nx) and floor(2^32 / ny), at most 2^32 - 1
 };
 
-// n / d and n mod d from r = min(floor(2^32 / d), 2^32 - 1): the estimate
+inline uint32_t div_reciprocal(uint32_t d) { return d == 1u ? 0xffffffffu : (uint32_t)((1ull << 32) / d); }
+
+// n / d and n mod d from r = div_reciprocal(d): the estimate
 // umulhi(n, r) is the quotient or one less, for every 32-bit n.
 __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t r, uint32_t& rem) {
   uint32_t q = __umulhi(n, r);
@@ -542,61 +544,91 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adjoint_min
 // single steps only in the order of the FP64 additions.  Small grids are
 // bound by the latency and the fixed cost of each launch, which this halves;
 // on large grids lambda^n never goes to HBM.
+//
+// One round of workgroups holds a 512^2 grid (two per CU), all of them in the
+// same phase, so what each phase waits for is not hidden by another workgroup's
+// work: the loads of a phase are issued before the barrier or the node ahead of
+// it, in 93 VGPRs (with f^{n-1} ahead of the second ring node too 512^2 gains
+// another 1 % and 500 x 333 loses 6).  D2Q9 FP32, u~ a field, us per launch with
+// each phase's loads at its start | ahead of it: 64^2 6.6 | 6.2, 512^2 12.9 |
+// 12.3, 500 x 333 11.2 | 10.4, 1448^2 91 | 86.5.  Tiles of 32 x 16 (a smaller
+// ring) take 13.2 us at 512^2, 32 x 32 with 1024 threads 13.1.
 constexpr int kA2X = 64, kA2Y = 8;
 constexpr int kA2RX = kA2X + 2, kA2RY = kA2Y + 2;  // ring region: lambda^n
 constexpr int kA2HX = kA2X + 4, kA2HY = kA2Y + 4;  // halo region: lambda^{n+1}
 
-__device__ __forceinline__ int wrap_index(int i, int n) {
-  int m = i % n;
-  return m < 0 ? m + n : m;
-}
-
 template <class B, int ST, int MODE, int RLX>
-__global__ __launch_bounds__(kA2X* kA2Y) void k_adjoint2(AdjArgs<typename Store<ST>::T> a) {
+__global__ __launch_bounds__(kA2X* kA2Y, 4) void k_adjoint2(AdjArgs<typename Store<ST>::T> a) {
   using L = typename B::Lat;
   using S = typename Store<ST>::S;
   using T = typename Store<ST>::T;
   constexpr int Q = B::Q;
   constexpr int D = L::D;
   static_assert(D == 2 && sizeof(T) == 4, "the two-step adjoint is for 2-D lattices with FP32 arithmetic");
-  constexpr int NT = kA2X * kA2Y;
-  __shared__ T lh[Q][kA2HY * kA2HX];  // lambda^{n+1}, halo region
-  __shared__ T lr[Q][kA2RY * kA2RX];  // lambda^n, ring region
-  __shared__ T gr[D][NT];             // step n's dJ/du~ at the owned nodes (field mode)
+  constexpr int NT = kA2X * kA2Y, NH = kA2HX * kA2HY, NR = kA2RX * kA2RY;
+  __shared__ T lh[Q][NH];  // lambda^{n+1}, halo region
+  __shared__ T lr[Q][NR];  // lambda^n, ring region
+  __shared__ T gr[D][NT];  // step n's dJ/du~ at the owned nodes (field mode)
   __shared__ double red[NT / 64][pow2_at_least(Q - D - 1)];
 
   const uint3 tile = block_tile(a.xcd_remap);
   const int tid = threadIdx.x;
-  const int nx = (int)a.nx, ny = (int)a.ny;
-  const int x0 = (int)tile.x * kA2X, y0 = (int)tile.y * kA2Y;
+  const uint32_t nx = a.nx, ny = a.ny;
+  const uint32_t x0 = tile.x * kA2X, y0 = tile.y * kA2Y;
   const uint64_t N = a.N;
+  // the node (periodic) at tile coordinates ix - 2, iy - 2
+  const uint32_t ox = x0 + (nx < 2 ? 2 : nx) - 2, oy = y0 + (ny < 2 ? 2 : ny) - 2;
+  auto node_at = [&](uint32_t ix, uint32_t iy) -> uint32_t {
+    uint32_t x, y;
+    div_by(ox + ix, nx, a.rnx, x);
+    div_by(oy + iy, ny, a.rny, y);
+    return y * nx + x;
+  };
+  // uniform base per population, 32-bit byte offset of the node (the host
+  // launches this kernel up to kAdj2MaxNodes)
+  auto at = [&](const auto* p, int j, uint32_t node) -> const auto* {
+    using E = std::remove_reference_t<decltype(*p)>;
+    return reinterpret_cast<const E*>(reinterpret_cast<const char*>(p + (uint64_t)j * N) + node * (uint32_t)sizeof(E));
+  };
   const S* fn = static_cast<const S*>(a.f);
   const S* fp = static_cast<const S*>(a.f_prev);
+  auto load_state = [&](const S* f, uint32_t node, T (&h)[Q], T (&utf)[3]) {
+    sfor<Q>([&](auto jj) { h[jj] = T(*at(f, jj, node)); });
+    if constexpr (MODE == UT_FIELD) {
+      sfor<D>([&](auto al) { utf[al] = T(*at(a.ut, al, node)) * a.inv_lambda; });
+    }
+  };
 
-  // lambda^{n+1} on the halo region
-  for (int i = tid; i < kA2HY * kA2HX; i += NT) {
-    const int ix = i % kA2HX, iy = i / kA2HX;
-    const uint64_t node = (uint64_t)wrap_index(y0 - 2 + iy, ny) * nx + wrap_index(x0 - 2 + ix, nx);
-    sfor<Q>([&](auto jj) { lh[jj][i] = a.lam_in[(uint64_t)jj * N + node]; });
-  }
+  // lambda^{n+1} on the halo region, and the state of step n's first nodes
+  // while it is on its way
+  constexpr int HR = (NH + NT - 1) / NT;
+  T st[HR][Q];
+  sfor<HR>([&](auto rr) {
+    const int i = tid + rr * NT;
+    if (i < NH) {
+      const uint32_t node = node_at((uint32_t)(i % kA2HX), (uint32_t)(i / kA2HX));
+      sfor<Q>([&](auto jj) { st[rr][jj] = *at(a.lam_in, jj, node); });
+    }
+  });
+  static_assert(NR >= NT && NR <= 2 * NT, "two ring nodes per thread at most");
+  T h1[Q], ut1[3] = {T(0), T(0), T(0)};
+  const int rx = tid % kA2RX, ry = tid / kA2RX;  // tile coordinates rx - 1, ry - 1
+  load_state(fn, node_at(rx + 1, ry + 1), h1, ut1);
+  sfor<HR>([&](auto rr) {
+    const int i = tid + rr * NT;
+    if (i < NH) sfor<Q>([&](auto jj) { lh[jj][i] = st[rr][jj]; });
+  });
   __syncthreads();
 
   double sacc[Q];
   sfor<Q>([&](auto kk) { sacc[kk] = 0.0; });
   // step n on the ring region
-  for (int i = tid; i < kA2RY * kA2RX; i += NT) {
-    const int ix = i % kA2RX, iy = i / kA2RX;  // tile coordinates ix - 1, iy - 1
-    const int gx = wrap_index(x0 - 1 + ix, nx), gy = wrap_index(y0 - 1 + iy, ny);
-    const uint64_t node = (uint64_t)gy * nx + gx;
-    T h[Q], g[Q], utf[3] = {T(0), T(0), T(0)};
+  auto ring_node = [&](int i, int ix, int iy, const T (&h)[Q], const T (&utf)[3]) {
+    T g[Q];
     sfor<Q>([&](auto jj) {
       constexpr int J = jj;
-      h[J] = T(fn[(uint64_t)J * N + node]);
       g[J] = lh[J][(iy + 1 + L::c[J].y) * kA2HX + (ix + 1 + L::c[J].x)];
     });
-    if constexpr (MODE == UT_FIELD) {
-      sfor<D>([&](auto al) { utf[al] = T(a.ut[(uint64_t)al * N + node]) * a.inv_lambda; });
-    }
     T lam[Q], gut[3], z3[Q], r[Q];
     adjoint_node<B, ST, MODE, RLX>(a, h, g, utf, lam, gut, z3, r);
     sfor<Q>([&](auto jj) { lr[jj][i] = lam[jj]; });
@@ -610,37 +642,49 @@ __global__ __launch_bounds__(kA2X* kA2Y) void k_adjoint2(AdjArgs<typename Store<
         sfor<D>([&](auto al) { gr[al][(iy - 1) * kA2X + (ix - 1)] = gut[al]; });
       }
     }
+  };
+  T h2[Q], ut2[3] = {T(0), T(0), T(0)};
+  const int i2 = tid + NT, sx = i2 % kA2RX, sy = i2 / kA2RX;
+  if (i2 < NR) load_state(fn, node_at(sx + 1, sy + 1), h2, ut2);
+  ring_node(tid, rx, ry, h1, ut1);
+  // the state of step n - 1, and the sums it is added to
+  const int tx = tid % kA2X, ty = tid / kA2X;
+  const uint32_t x = x0 + tx, y = y0 + ty, own = y * nx + x;
+  const bool active = x < nx && y < ny;
+  if (i2 < NR) ring_node(i2, sx, sy, h2, ut2);
+  T h[Q], utf[3] = {T(0), T(0), T(0)};
+  double sum_ut[D];
+  if (active) {
+    sfor<Q>([&](auto jj) { h[jj] = T(__builtin_nontemporal_load(at(fp, jj, own))); });
+    if constexpr (MODE == UT_FIELD) {
+      sfor<D>([&](auto al) {
+        utf[al] = T(*at(a.ut, al, own)) * a.inv_lambda;
+        sum_ut[al] = *at(a.grad_ut, al, own);
+      });
+    }
   }
   __syncthreads();
 
   // step n - 1 on the owned tile
-  const int tx = tid % kA2X, ty = tid / kA2X;
-  const int x = x0 + tx, y = y0 + ty;
-  if (x < nx && y < ny) {
-    const uint64_t node = (uint64_t)y * nx + x;
-    T h[Q], g[Q], utf[3] = {T(0), T(0), T(0)};
+  if (active) {
+    T g[Q];
     sfor<Q>([&](auto jj) {
       constexpr int J = jj;
-      h[J] = T(__builtin_nontemporal_load(&fp[(uint64_t)J * N + node]));
       g[J] = lr[J][(ty + 1 + L::c[J].y) * kA2RX + (tx + 1 + L::c[J].x)];
     });
-    if constexpr (MODE == UT_FIELD) {
-      sfor<D>([&](auto al) { utf[al] = T(a.ut[(uint64_t)al * N + node]) * a.inv_lambda; });
-    }
     T lam[Q], gut[3], z3[Q], r[Q];
     adjoint_node<B, ST, MODE, RLX>(a, h, g, utf, lam, gut, z3, r);
-    sfor<Q>([&](auto jj) { __builtin_nontemporal_store(lam[jj], &a.lam_out[(uint64_t)jj * N + node]); });
+    sfor<Q>([&](auto jj) { __builtin_nontemporal_store(lam[jj], const_cast<T*>(at(a.lam_out, jj, own))); });
     sfor<Q>([&](auto kk) {
       constexpr int K = kk;
       if constexpr (K > D) sacc[K] += double(z3[K]) * double(r[K]);
     });
     if constexpr (MODE == UT_FIELD) {
       sfor<D>([&](auto al) {
-        double* gp = &a.grad_ut[(uint64_t)al * N + node];
-        double v = *gp;
+        double v = sum_ut[al];
         v += double(gr[al][tid] * a.inv_lambda);
         v += double(gut[al] * a.inv_lambda);
-        *gp = v;
+        *const_cast<double*>(at(a.grad_ut, al, own)) = v;
       });
     }
   }

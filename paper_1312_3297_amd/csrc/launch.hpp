@@ -362,9 +362,8 @@ hipError_t launch_adjoint_t(const AdjLaunch& L) {
   a.rnninv = static_cast<const T*>(L.rnninv);
   a.xcd_remap = L.xcd_remap;
   a.eq_maxwell = L.eq_maxwell;
-  auto reciprocal = [](uint32_t d) { return d == 1u ? 0xffffffffu : (uint32_t)((1ull << 32) / d); };
-  a.rnx = reciprocal(L.nx);
-  a.rny = reciprocal(L.ny);
+  a.rnx = div_reciprocal(L.nx);
+  a.rny = div_reciprocal(L.ny);
   const dim3 grid((unsigned)((L.N + 255) / 256));
   hipLaunchKernelGGL((k_adjoint<B, ST, MODE, RLX>), grid, dim3(256), 0, L.stream, a);
   return hipGetLastError();
@@ -408,6 +407,8 @@ hipError_t launch_adjoint2_t(const AdjLaunch& L) {
   a.rnninv = static_cast<const T*>(L.rnninv);
   a.xcd_remap = L.xcd_remap;
   a.eq_maxwell = L.eq_maxwell;
+  a.rnx = div_reciprocal(L.nx);
+  a.rny = div_reciprocal(L.ny);
   dim3 grid((L.nx + kA2X - 1) / kA2X, (L.ny + kA2Y - 1) / kA2Y, 1);
   hipLaunchKernelGGL((k_adjoint2<B, ST, MODE, RLX>), grid, dim3(kA2X * kA2Y), 0, L.stream, a);
   return hipGetLastError();

@@ -94,7 +94,8 @@ def test_tiles_in_space_equal_single_steps(lattice, storage, shape):
 
 # two steps per launch on 3-D grids: chunks of one plane count and with a short
 # last one, tiles of each number of rows (FP32: 20 with 257 rows), tiles that
-# divide an extent and that leave a remainder, few planes; the last of each list is below the bound on idle columns (single steps)
+# divide an extent and that leave a remainder, few planes; the last of each list
+# is below the bound on idle columns (single steps)
 PAIRS = {"d3q19": [(70, 64, 64), (5, 161, 193), (131, 31, 64), (16, 97, 128), (8, 257, 250), (301, 17, 33)],
          "d3q27": [(80, 80, 81), (101, 77, 66), (7, 305, 257), (8, 257, 250), (900, 24, 28)]}
 
@@ -147,6 +148,24 @@ def test_reverse_step_over_whole_rows(shape, mode):
     torch.cuda.synchronize()
     for got, ref in ((gfg, gf), (gsg, gs)) + (((gug, gu),) if mode == "field" else ()):
         assert np.abs(got.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("shape", [(200, 1), (37, 2), (5, 3), (2, 65), (17, 66), (8, 127)])
+def test_reverse_pairs_on_narrow_grids(shape):
+    """Two reverse steps per launch where the two-node halo wraps several times
+    in x or the last tile holds one or two columns: dJ/df0 and dJ/du~ bit for
+    bit those of single steps (K = 1), dJ/ds to the order of FP64 sums."""
+    lat = oracle_lattice("d2q9")
+    rng = np.random.default_rng(48)
+    st, _ = to_storage(lat, far_state(lat, shape, seed=49, amp=0.02, umax=0.05), "f32")
+    ctx = Lbmrv("d2q9", RATES["d2q9"], tuple(reversed(shape)), "f32")
+    gpu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    cot = gpu(rng.standard_normal((9,) + shape).astype(np.float32))
+    field = gpu(rng.uniform(-0.1, 0.1, (2,) + shape).astype(np.float32))
+    single, paired = (ctx.adjoint(gpu(st), cot, 7, K, "field", field) for K in (1, 7))
+    torch.cuda.synchronize()
+    assert torch.equal(single[1], paired[1]) and torch.equal(single[3], paired[3])
+    assert torch.allclose(single[2], paired[2], rtol=1e-13, atol=1e-13 * float(single[2].abs().max()))
 
 
 @pytest.mark.parametrize("lattice,shape", [("d2q9", (1, 1)), ("d2q9", (1, 7)), ("d2q9", (16, 32)), ("d2q9", (19, 27)),

@@ -125,7 +125,8 @@ struct lbmrv_ctx {
   int entry;      // index into kEntries
   int sk;         // StorageKind
   int streaming;  // LBMRV_STREAM_*
-  int block;
+  TilePlan tile;    // how the kernels of several steps per launch cover the grid
+  SlidePlan slide;
   double lambda;
   double s[27];
   uint32_t nx, ny, nz;
@@ -212,7 +213,8 @@ StepLaunch base_launch(const lbmrv_ctx* c, hipStream_t st) {
   L.relax = c->custom ? c->dtab : nullptr;
   L.xcd_remap = xcd_order(c);
   L.stream = st;
-  L.block = c->block;
+  L.tile = c->tile;
+  L.slide = c->slide;
   return L;
 }
 
@@ -247,7 +249,7 @@ struct Fused {
   int64_t steps;
 };
 Fused fused_kind(const lbmrv_ctx* c) {
-  const bool slides = kEntries[c->entry].slide[c->sk](c->nx, c->ny, c->nz).chunk != 0;
+  const bool slides = c->slide.chunk != 0;
   if (c->wall_mask) {
     // k_slide has walls on x and y faces, for the built-in bases; on both faces of
     // an axis, as its last launch scatters (past a single wall, the slot a node
@@ -257,8 +259,7 @@ Fused fused_kind(const lbmrv_ctx* c) {
     if (slides && !(m >> 4) && paired && !c->custom && slide_walls(c->q, (int)elem_bytes(c->storage))) return {K_SLIDE, 2};
     return {K_PUSH, 1};
   }
-  const TilePlan tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
-  if (tile.steps >= 2) return {K_TILE, tile.steps};
+  if (c->tile.steps >= 2) return {K_TILE, c->tile.steps};
   return slides ? Fused{K_SLIDE, 2} : Fused{K_PUSH, 1};
 }
 
@@ -709,13 +710,14 @@ int lbmrv_create(lbmrv_ctx** out, int lattice, int basis, double lambda, const d
   c->entry = lattice == LBMRV_D2Q9 ? (basis == LBMRV_BASIS_GEIER ? 1 : 0) : lattice == LBMRV_D3Q19 ? 2 : 3;
   c->sk = storage == LBMRV_F64 ? SK_F64 : storage == LBMRV_F16DEV ? SK_F16 : SK_F32;
   c->streaming = LBMRV_STREAM_PULL;
-  c->block = 256;
   c->lambda = lambda;
   for (int k = 0; k < 27; ++k) c->s[k] = k < q ? s[k] : 0.0;
   c->nx = (uint32_t)e[0];
   c->ny = (uint32_t)e[1];
   c->nz = (uint32_t)e[2];
   c->N = N;
+  c->tile = kEntries[c->entry].tile[c->sk](c->nx, c->ny, c->nz);
+  c->slide = kEntries[c->entry].slide[c->sk](c->nx, c->ny, c->nz);
   c->rho0 = (storage == LBMRV_F32DEV || storage == LBMRV_F16DEV) ? rho0 : 0.0;
   *out = c;
   return LBMRV_OK;
@@ -1325,7 +1327,6 @@ int lbmrv_adjoint(lbmrv_ctx* c, const void* f0, int ut_mode, double ut_alpha, co
   A.xcd_remap = xcd_order(c);
   A.eq_maxwell = c->equilibrium == LBMRV_EQ_MAXWELLIAN ? 1u : 0u;
   A.stream = st;
-  A.block = c->block;
   const bool two_step = has_adjoint2(c->d, c->sk) && c->N <= kAdj2MaxNodes;
   const void* lam_cur = cot_fN;
   // Reverse sweep, one segment of K steps at a time, last segment first (its

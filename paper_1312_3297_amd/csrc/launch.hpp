@@ -32,11 +32,12 @@ struct StepLaunch {
   const void* relax;  // run-time basis: R^{-1} S R block in the arithmetic type, or null
   uint32_t xcd_remap; // block order (see block_tile)
   hipStream_t stream;
-  int block;   // threads per block along x
   uint64_t steps;            // K_TILE, K_CLOSED: steps of this launch
   uint32_t gather, scatter;  // K_TILE, K_SLIDE: as in TileArgs
   void* keep;                // K_TILE, K_SLIDE: as in TileArgs
   uint64_t keep_stride;      // K_TILE: elements between kept states
+  TilePlan tile;             // K_TILE, K_SLIDE: the context's plans
+  SlidePlan slide;
 };
 
 struct MomLaunch {
@@ -154,7 +155,7 @@ hipError_t launch_step_t(const StepLaunch& L) {
 template <class B, int ST, int MODE, int RLX>
 hipError_t launch_tile_t(const StepLaunch& L) {
   static_assert(tile_lds_bytes<B, ST, MODE>() <= kLdsPerCu, "the region of a tile fits in LDS");
-  const TilePlan p = plan_tile<B, ST>(L.nx, L.ny, L.nz);
+  const TilePlan& p = L.tile;
   if (L.steps < 1 || L.steps > p.steps) return hipErrorInvalidValue;
   TileArgs g{};
   g.steps = (uint32_t)L.steps;
@@ -170,17 +171,19 @@ hipError_t launch_tile_t(const StepLaunch& L) {
   }
   StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
   dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.t[2] - 1) / p.t[2]);
+  uint32_t threads = p.threads;
+  if ((uint64_t)grid.x * grid.y * grid.z > 256) threads = std::min(threads, tile_threads_shared<B::Lat::D, ST, MODE>());
   if (L.keep)
-    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX, true>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX, true>), grid, dim3(threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
   else
-    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX, false>), grid, dim3(p.threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
+    hipLaunchKernelGGL((k_tile<B, ST, MODE, RLX, false>), grid, dim3(threads), (tile_lds_bytes<B, ST, MODE>()), L.stream, a, g);
   return hipGetLastError();
 }
 
 template <class B, int ST, int MODE, int RLX>
 hipError_t launch_slide_t(const StepLaunch& L) {
   if constexpr (B::Lat::D == 3 && ST != 2) {
-    const SlidePlan p = plan_slide<B, ST>(L.nx, L.ny, L.nz);
+    const SlidePlan& p = L.slide;
     if (!p.chunk) return hipErrorInvalidValue;
     SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter, L.keep};
     StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
@@ -336,7 +339,6 @@ struct AdjLaunch {
   uint32_t xcd_remap;
   uint32_t eq_maxwell;
   hipStream_t stream;
-  int block;
 };
 
 template <class B, int ST, int MODE, int RLX>

@@ -77,20 +77,42 @@ template <class B, int ST>
 TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
   using Sh = TileShape<B, ST>;
   const uint32_t n[3] = {nx, ny, nz};
-  const uint64_t nodes = (uint64_t)nx * ny * nz;
   TilePlan p{{1, 1, 1}, 0, 0};
   if constexpr (B::Lat::D == 2) {
     // Large tiles waste less on the ring (32 x 32, 5 steps: 27 % more node
-    // steps; 16 x 16: 57 %), small ones keep the 256 CUs busy on small grids.
-    // Measured, us per step, D2Q9 FP32 (one step per launch | 8 | 16 | 32):
-    //   64^2    3.6 | 1.2 | 1.5 |  -      256^2   4.0 |  2  | 1.6 | 2.5
-    //   512^2   4.8 |  -  | 3.6 | 2.8     2048^2 54.5 | 136 |  50 | 27.5
-    const uint32_t s = nodes >= 3u << 16 ? 32u : nodes >= 1u << 15 ? 16u : 8u;
-    p.steps = s == 32u ? 5u : 8u;
-    fit_tile(p, 2, n, {s, s, 1u});
-    // one workgroup per CU wants a thread per region node, two share the CU
-    const uint64_t groups = (uint64_t)((nx + p.t[0] - 1) / p.t[0]) * ((ny + p.t[1] - 1) / p.t[1]);
-    p.threads = s == 32u ? (groups <= 256u ? 1024u : 768u) : s == 16u ? 768u : 512u;
+    // steps; 16 x 16: 57 %), small ones keep the 256 CUs busy on small grids, more
+    // steps take fewer launches.  The plan is the one of least cost per step, in
+    // units of a wavefront's pass over one region node per lane (62 ns FP32, 80 ns
+    // FP64): 64 for a launch that fills at most one workgroup per CU, or 72 per
+    // round for its loads and stores, 5 per step, and the wavefronts of all steps;
+    // two workgroups that share a CU hide a quarter of each other's time.  Within
+    // 8 % of what these measured, us per step, FP32 (tile, steps): 256^2 (16 x 16,
+    // 7) 1.37, 384^2 (24 x 24, 7) 1.79 and (16 x 16, 7) 2.6, 512^2 (32 x 32, 5)
+    // 2.38, 640^2 (30 x 30, 6) 3.3 and (32 x 32, 5) 3.6, 724^2 (28 x 28, 7) 4.3 and
+    // (32 x 32, 5) 5.1, 1024^2 (32 x 32, 5) 6.6 and (30 x 30, 6) 7.1.  The search
+    // takes some 10 us: once per context.
+    constexpr bool shared = ST != 0;  // two workgroups fit in a CU's LDS
+    constexpr uint32_t sides[] = {32, 30, 28, 24, 20, 16, 12, 8, 4};  // of equal plans the widest in x
+    double best = 1e300;
+    for (uint32_t sx : sides)
+      for (uint32_t sy : sides) {
+        const uint32_t cx = (nx + sx - 1) / sx, cy = (ny + sy - 1) / sy;
+        const uint32_t tx = (nx + cx - 1) / cx, ty = (ny + cy - 1) / cy;  // no nearly empty last row
+        const uint64_t rounds = ((uint64_t)cx * cy + 255) / 256;
+        double waves = 0;
+        for (uint32_t k = 1; k <= kTileMaxSteps; ++k) {
+          const uint32_t r = 2 * (k - 1), region = (tx + r) * (ty + r);
+          if (tx + r > (uint32_t)Sh::PX || ty + r > (uint32_t)Sh::PY || tx + k - 1 > nx || ty + k - 1 > ny) break;
+          waves += (region + 63) / 64;
+          if (k < 2) continue;
+          const double work = rounds == 1 ? 64 + waves : (72 + waves) * (double)rounds * (shared ? 0.75 : 1.0);
+          const double cost = (work + 5.0 * k) / k;
+          if (cost < best) {
+            best = cost;
+            p = {{tx, ty, 1}, k, region < 1024 ? (region + 63) / 64 * 64 : 1024u};
+          }
+        }
+      }
     return p;
   } else {
     // In space the ring is dear (16 x 8 x 8, two steps: 38 % more node steps;
@@ -126,9 +148,20 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
       if (p.threads > most) p.threads = most;
       return p;
     }
-    (void)nodes;
     return p;
   }
+}
+
+// Threads per workgroup where the grid has more than 256 tiles, at most the
+// plan's.  One workgroup per CU wants a thread per region node, and so do two
+// whose waves all fit; with u~ a field (FP32) two of 768 do better, and FP16,
+// whose regions leave room for three or four workgroups, takes 512.  2-D, us per
+// launch with 1024 | 768 | 512 threads: FP32 u~ = u 1024^2 29.9 | 31.0 | -, a
+// field 40.1 | 32.4 | 34.7; FP16 u~ = 0 2048^2 99 | 103 | 90, a field 151 | 118 |
+// 108; FP64 a field 61.4 | 62.3 | 66.9.
+template <int D, int ST, int MODE>
+constexpr uint32_t tile_threads_shared() {
+  return D != 2 || ST == 0 ? 1024u : ST == 2 ? 512u : MODE == UT_FIELD ? 768u : 1024u;
 }
 
 template <class B, int ST, int MODE>

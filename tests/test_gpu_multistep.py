@@ -62,10 +62,10 @@ def compare(lattice, shape, storage, mode, steps, basis="default", equilibrium="
             assert torch.equal(b.view(bits), want[n - 1].view(bits)), (kind, n)
 
 
-# 2-D grids (ny, nx): around the smallest tiled extent, remainders of every
-# tile size, the thresholds between tile sizes (2^15 and 3 * 2^16 nodes), thin grids
+# 2-D grids (ny, nx): around the smallest tiled extent, tiles of each size and of
+# unequal sides, remainders, one round of workgroups and more, thin grids
 @pytest.mark.parametrize("shape", [(8, 40), (9, 9), (10, 300), (15, 16), (31, 33), (64, 64), (173, 190), (16, 2049),
-                                   (429, 458), (440, 450), (33, 6000), (36, 6001)])
+                                   (300, 301), (429, 458), (440, 450), (601, 590), (33, 6000), (36, 6001)])
 @pytest.mark.parametrize("storage", ["f64", "f32", "f32dev", "f16dev"])
 def test_tiles_equal_single_steps(shape, storage):
     compare("d2q9", shape, storage, "fluid", (1, 2, 5, 8, 17), streaming=("pull",))
@@ -77,7 +77,7 @@ def test_tiles_equal_single_steps(shape, storage):
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
 def test_tiles_in_every_mode_and_basis(basis, mode, equilibrium, storage):
     b, rates = (workloads.RAW_D2Q9, workloads.RATES_RAW_D2Q9) if basis == "custom" else (basis, None)
-    for shape in ((21, 37), (190, 200), (450, 449)):
+    for shape in ((21, 37), (190, 200), (450, 449), (601, 590)):
         compare("d2q9", shape, storage, mode, (2, 7, 12), b, equilibrium, rates)
 
 

@@ -449,7 +449,7 @@ __device__ __forceinline__ void adjoint_node(const AdjArgs<typename Store<ST>::T
 
 // One reverse step.  A workgroup takes 256 consecutive nodes of the grid,
 // whatever its rows: with workgroups along one row a 64-wide grid left 192 of
-// 256 threads without a node of their own (D3Q19 64^3 FP32: 53 us a step).
+// 256 threads without a node of their own (D3Q19 64^3 FP32: 45 -> 14 us a step).
 // D3Q19 with FP32 arithmetic and u~ = u took 129 registers, one past the 128
 // that let a SIMD hold four of its wavefronts, so four are asked for.
 template <class B, int ST>
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kA2X* kA2Y, 4) void k_adjoint2(AdjArgs<typename Sto
     return y * nx + x;
   };
   // uniform base per population, 32-bit byte offset of the node (the host
-  // launches this kernel up to kAdj2MaxNodes)
+  // launches this kernel up to 2^28 nodes)
   auto at = [&](const auto* p, int j, uint32_t node) -> const auto* {
     using E = std::remove_reference_t<decltype(*p)>;
     return reinterpret_cast<const E*>(reinterpret_cast<const char*>(p + (uint64_t)j * N) + node * (uint32_t)sizeof(E));

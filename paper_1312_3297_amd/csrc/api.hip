@@ -1140,13 +1140,20 @@ namespace {
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Grids up to this many nodes reverse two steps per launch (k_adjoint2) where
-// the lattice has that kernel: small grids are bound by each launch's latency
-// and fixed cost.  Measured (D2Q9 FP32, u~ a field, K = 100), two steps per
-// launch against one: 512^2 -16 %, 724^2 -9 %, 1024^2 -5 %, 1448^2 -1.3 %,
-// 2048^2 +4.6 % (there HBM bounds both, and the single-step kernel runs more
-// wavefronts per SIMD).
-constexpr uint64_t kAdj2MaxNodes = 1ull << 21;
+// Whether a grid is reversed two steps per launch (k_adjoint2) where the lattice
+// has that kernel.  Up to 2^21 nodes: small grids are bound by each launch's
+// latency and fixed cost.  Beyond 2^22 with u~ a field: there the single step
+// moves 148 bytes per node from HBM and two in one launch 110 each, and the
+// states no longer fit in the last-level cache; without the field's 24 bytes the
+// vector ALU weighs as much.  us for two steps, one | two per launch, D2Q9 FP32,
+// a field: 512^2 15.3 | 12.2, 1448^2 86.0 | 86.4, 2048^2 162 | 175, 2900^2 428 |
+// 370, 4096^2 816 | 662; u~ = u: 512^2 13.7 | 11.1, 1448^2 72 | 76, 2048^2 135 |
+// 149, 2900^2 293 | 313, 4096^2 584 | 560.  Up to 2^28 nodes, as the kernel's
+// byte offsets are 32-bit.
+bool adjoint_pairs(const lbmrv_ctx* c, int mode) {
+  if (!has_adjoint2(c->d, c->sk)) return false;
+  return c->N <= 1ull << 21 || (mode == UT_FIELD && c->N > 1ull << 22 && c->N <= 1ull << 28);
+}
 
 struct AdjPlan {
   int64_t nseg, nsnap, nsegslots, nsets;
@@ -1327,7 +1334,7 @@ int lbmrv_adjoint(lbmrv_ctx* c, const void* f0, int ut_mode, double ut_alpha, co
   A.xcd_remap = xcd_order(c);
   A.eq_maxwell = c->equilibrium == LBMRV_EQ_MAXWELLIAN ? 1u : 0u;
   A.stream = st;
-  const bool two_step = has_adjoint2(c->d, c->sk) && c->N <= kAdj2MaxNodes;
+  const bool two_step = adjoint_pairs(c, ut_mode);
   const void* lam_cur = cot_fN;
   // Reverse sweep, one segment of K steps at a time, last segment first (its
   // states are in place from the forward sweep).  Segment sg waits for its

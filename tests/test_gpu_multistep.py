@@ -168,6 +168,13 @@ def test_reverse_pairs_on_narrow_grids(shape):
     assert torch.allclose(single[2], paired[2], rtol=1e-13, atol=1e-13 * float(single[2].abs().max()))
 
 
+@pytest.mark.parametrize("shape", [(2049, 2050), (1, 2 ** 22 + 1)])
+def test_reverse_pairs_on_large_grids(shape):
+    """The first grids beyond 2^22 nodes, in two-step launches again: bit for bit
+    single steps, as on narrow grids."""
+    test_reverse_pairs_on_narrow_grids(shape)
+
+
 @pytest.mark.parametrize("lattice,shape", [("d2q9", (1, 1)), ("d2q9", (1, 7)), ("d2q9", (16, 32)), ("d2q9", (19, 27)),
                                            ("d3q19", (1, 2, 3)), ("d3q19", (8, 8, 8)), ("d3q27", (7, 8, 9))])
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])

@@ -404,7 +404,17 @@ hipError_t run_advance(const lbmrv_ctx* c, const void* src, void* dst, int64_t n
 template <class State>
 hipError_t run_keeping(const lbmrv_ctx* c, State state, int64_t n, size_t keep_bytes, int mode, double alpha,
                        const float* ut, hipStream_t st) {
-  const Fused f = fused_kind(c);
+  Fused f = fused_kind(c);
+  // Every state goes to memory, so several steps per launch save half of the
+  // traffic at best, and rows that are no whole 32-byte sectors (whole 128-byte
+  // lines where a state exceeds the 256 MB last-level cache) lose that again: a
+  // tile stores pieces of them with other tiles' pieces in between, a single step
+  // whole rows.  Past the sizes that launches bound, such grids keep single steps.
+  // ms, reverse sweep included, u~ = u, several | single, 40 steps: D2Q9 FP16 1448^2
+  // 3.09 | 2.45, FP32 2100^2 7.52 | 6.35, 1001 x 999 1.59 | 1.47, D3Q19 FP32 201 x
+  // 117 x 83 7.27 | 6.63; 20 steps: D2Q9 FP32 3000 x 3001 8.44 | 6.64.
+  const size_t eb = elem_bytes(c->storage), whole = (uint64_t)c->q * c->N * eb > 256u << 20 ? 128 : 32;
+  if (c->N >= 1u << 18 && c->nx * eb % whole != 0) f = {K_PUSH, 1};
   StepLaunch L = base_launch(c, st);
   L.mode = mode;
   L.alpha = alpha;

@@ -12,9 +12,10 @@ the current stream, bracketed by a device synchronisation; inputs are resident
 in HBM before the timed region.  Prints one JSON line.  roofline.achieved is
 the algorithmic bytes of one step (2 q b per node, plus the u~ field when it is
 read) over the measured time per step; roofline.per_launch gives the same per
-kernel launch (they differ only when a call adds boundary passes: the pull
-form's first collision and last transport, the in-place form's final swap
-after an odd step count).
+kernel launch of the in-place form (they differ only by its final swap after
+an odd step count).  With two arrays (--streaming pull or push) the library
+takes several steps per launch where that is faster, so one launch is no fixed
+number of steps and per_launch is null.
 """
 import argparse
 import json
@@ -34,7 +35,8 @@ HBM_PEAK_GBS = 8000.0
 # FETCH_SIZE and WRITE_SIZE counters scaled by what the same counters read for
 # a plain copy of known size (FETCH x 2.0, WRITE x 1.0); see profiles/.  Only
 # valid for the kernel version the counters were taken on, in the default
-# (automatic) block order; the in-place form averages its two kernels.
+# (automatic) block order; the in-place form averages its two kernels.  With two
+# arrays only the FP16 workloads still take one step per launch.
 TRAFFIC_GB = {
     ("d2q9_shear2048_f32_fluid", "aa"): 0.3021,
     ("d2q9_shear4096_f32_fluid", "aa"): 1.2395,
@@ -47,18 +49,8 @@ TRAFFIC_GB = {
     ("d3q19_tgv512_f32_fluid", "aa"): 20.8212,
     ("d3q27_tgv192_f16dev_field", "aa"): 0.8495,
     ("d3q27_tgv192_f32_field", "aa"): 1.6143,
-    ("d2q9_shear2048_f32_fluid", "pull"): 0.3021,
-    ("d2q9_shear4096_f32_fluid", "pull"): 1.2207,
-    ("d3q19_couette256_f32_fluid_walls", "pull"): 2.5533,
     ("d3q19_tgv256_f16dev_fluid", "pull"): 1.2752,
-    ("d3q19_tgv256_f32_fluid", "pull"): 2.5508,
-    ("d3q19_tgv256_f32_fluid", "push"): 2.551,
-    ("d3q19_tgv256_f32_fluid_rawbasis", "pull"): 2.5512,
-    ("d3q19_tgv256_f32dev_fluid", "pull"): 2.5508,
-    ("d3q19_tgv256_f64_fluid", "pull"): 5.1006,
-    ("d3q19_tgv512_f32_fluid", "pull"): 21.0724,
     ("d3q27_tgv192_f16dev_field", "pull"): 0.8731,
-    ("d3q27_tgv192_f32_field", "pull"): 1.6595,
 }
 
 WORKLOADS = {
@@ -332,14 +324,13 @@ def main():
     N = ctx.N
     q = ctx.q
     b = {"f64": 8, "f32": 4, "f32dev": 4, "f16dev": 2}[storage]
-    # kernel launches inside the call: pull = collide + (K-1) fused + transport;
-    # push = K fused (+ one split step when K is even); in place = K (+ one swap
-    # pass when K is odd).  Every launch reads and writes q populations per node
-    # (the swap pass a little less).
-    launches = {"pull": K + 1, "push": K if K % 2 else K + 1, "aa": K + (K % 2)}[args.streaming]
+    # kernel launches inside the call: in place K (+ one swap pass when K is odd;
+    # every launch reads and writes q populations per node, the swap pass a little
+    # less); with two arrays the library's choice
+    launches = K + (K % 2) if args.streaming == "aa" else None
     bytes_per_step = 2 * q * b * N + (ctx.d * 4 * N if mode == "field" else 0)
     achieved = bytes_per_step * K / (ms * 1e-3) / 1e9
-    achieved_launch = bytes_per_step * launches / (ms * 1e-3) / 1e9
+    achieved_launch = bytes_per_step * launches / (ms * 1e-3) / 1e9 if launches else None
     mlups = N * K / (ms * 1e-3) / 1e6
     out = {
         "metric": METRIC,
@@ -362,7 +353,7 @@ def main():
                      "traffic": TRAFFIC_GB.get((name, args.streaming)) if args.block_order == "auto" else None,
                      "bytes_per_step_GB": round(bytes_per_step / 1e9, 4),
                      "per_launch": {"launches": launches, "achieved": round(achieved_launch, 1),
-                                    "frac": round(achieved_launch / HBM_PEAK_GBS, 4)}},
+                                    "frac": round(achieved_launch / HBM_PEAK_GBS, 4)} if launches else None},
         "state_finite": bool(finite),
         "wall_s": round(wall, 4),
     }

@@ -54,8 +54,10 @@
  * a faster path in the in-place form; results are the same bits).  A
  * `hip_stream` argument is a hipStream_t (NULL = the null stream); work is
  * enqueued on it asynchronously unless stated otherwise.  The context owns only
- * its parameters, (after the first lbmrv_conservation call) a small device
- * buffer for partial sums and, for a run-time basis, a small device table.
+ * its parameters, (after the first lbmrv_conservation or lbmrv_deviation_norm
+ * call) a small device buffer for partial sums and a few bytes of host memory
+ * that the GPU writes the totals to and, for a run-time basis, a small device
+ * table.
  *
  * Concurrency.  A context is not thread-safe: calls on one context must not
  * run concurrently from several host threads.  lbmrv_conservation and
@@ -171,6 +173,13 @@ int lbmrv_set_rates(lbmrv_ctx *c, const double *s);
  *     odd steps gather from the opposite slots upstream and scatter downstream;
  *     an odd step count ends with one swap pass.  lbmrv_step then accepts
  *     f_in == f_out (otherwise f_in is first copied to f_out).
+ * With two arrays a call of several steps takes as many per kernel launch as
+ * suit the grid, whichever of the two forms is selected (the order of the
+ * launches is then the library's own): 2-D grids and small 3-D ones 2 to 8,
+ * larger 3-D ones in FP64 and FP32 storage 2, with walls only D3Q19 in FP32
+ * storage and walls on both faces of the x or y axis.  Grids of at most 512
+ * nodes take all steps in one launch, in every form (in place without the
+ * copy of f_in).  f_in is overwritten as before.
  * No HIP call.
  */
 int lbmrv_set_streaming(lbmrv_ctx *c, int kind);

@@ -376,7 +376,7 @@ __device__ __forceinline__ void cube_populations_t(const T (&g)[B::Q], T (&zm)[B
 // share all of it.  For eq. (mom) on D2Q9 that is 32 + 37 operations for the two
 // maps instead of 54 + 57, each a sum over the same terms with the same
 // coefficients.  FP64 only: there the regrouping moves results by a few 1e-16
-// (D2Q9 by k_tile: 2048^2 52.7 -> 50.3 us a step, 64^2 1.30 -> 1.26), in FP32 it
+// (D2Q9 by k_tile, same tiles: 2048^2 52.7 -> 50.3 us a step, 64^2 1.30 -> 1.26), in FP32 it
 // moved the rate gradients of the adjoint, differences of nearly equal FP32
 // values, by 1e-2.
 template <class B>
@@ -1216,7 +1216,8 @@ __device__ __forceinline__ void reduce_row(const double (&acc)[NV], const RedOut
 // Sums of the populations and of c_j times them, and the number of non-finite
 // ones.  A node's sum of all populations tells whether it holds one, so they
 // are counted one by one only then: testing each cost as much as the sums
-// (D3Q19 256^3 FP32: 256 -> 226 us, 5.6 TB/s).
+// (D3Q19 256^3 FP32: 244 -> 190 us, 6.7 TB/s of q b N, part of it from the
+// last-level cache).
 template <class B, int ST>
 __global__ __launch_bounds__(kRedThreads) void k_conserve_partial(const void* fp, uint64_t N, RedOut o) {
   using L = typename B::Lat;

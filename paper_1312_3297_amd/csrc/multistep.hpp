@@ -123,15 +123,21 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
     //   D3Q19 FP32  16^3 5.1 | 2.6  32^3 5.2 | 3.2  48^3 5.9 | 5.0  64^3 9.0 | 7.0
     //   D3Q19 FP64  16^3 6.5 | 3.0  32^3 6.0 | 4.4  48^3 10.4 | 7.3
     //   D3Q27 FP32  16^3 6.0 | 4.2  32^3 5.5 | 4.8  48^3 7.2 | 7.4
+    // A fused pass takes its time however many of the 256 CUs it fills, a single
+    // one less on a smaller grid, hence the least nodes of the larger tiles: D3Q19
+    // FP32 101 x 49 x 15 (12 x 6 x 6) 4.9 | 5.9, 64 x 20 x 73 (16 x 8 x 8) 4.8 |
+    // 6.4, FP64 45 x 22 x 49 (12 x 6 x 6) 5.4 | 6.4, D3Q27 FP64 32 x 29 x 17 (8 x
+    // 4 x 4) 5.5 | 6.3, FP16 with a field 32 x 10 x 53 4.0 | 4.6.
     struct Side {
       uint32_t s[3];
       uint32_t steps;
+      uint64_t least;
     };
     constexpr bool f64 = ST == 0, q27 = B::Q == 27;
-    const Side sides[4] = {{{4, 4, 4}, q27 ? 2u : 3u},
-                           {{8, 4, 4}, q27 || f64 ? 2u : 4u},
-                           {{12, 6, 6}, 2u},
-                           {{16, 8, 8}, 2u}};
+    const Side sides[4] = {{{4, 4, 4}, q27 ? 2u : 3u, 0},
+                           {{8, 4, 4}, q27 || f64 ? 2u : 4u, q27 && ST != 1 ? ~0ull : 0},
+                           {{12, 6, 6}, 2u, f64 ? 1u << 16 : 5u << 14},
+                           {{16, 8, 8}, 2u, 9u << 14}};
     for (const Side& c : sides) {
       const uint32_t r = 2 * (c.steps - 1);
       if (c.s[0] + r > (uint32_t)Sh::PX || c.s[1] + r > (uint32_t)Sh::PY || c.s[2] + r > (uint32_t)Sh::PZ) break;
@@ -140,6 +146,7 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
       uint64_t groups = 1;
       for (int a = 0; a < 3; ++a) groups *= (n[a] + c.s[a] - 1) / c.s[a];
       if (groups > 256) continue;
+      if ((uint64_t)nx * ny * nz < c.least) return p;
       p.steps = c.steps;
       if (!fit_tile(p, 3, n, c.s)) return p;
       const uint32_t q = 2 * (p.steps - 1), region = (p.t[0] + q) * (p.t[1] + q) * (p.t[2] + q);
@@ -320,7 +327,8 @@ __global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<t
 // step scatters to the natural layout.  Every load from fin comes before the
 // first store to fout, so the two may be the same array.  A step costs the
 // latency of one collision and one LDS exchange, which a second wavefront per
-// SIMD hides half of; D2Q9 16^2 FP64, 50 steps: 82 us by k_tile (7 launches).
+// SIMD hides half of; D2Q9 16^2 FP64, 50 steps: 32 us, and 82 by k_tile (7
+// launches).
 constexpr uint32_t kClosedNodes = 512;
 
 template <class B, int ST, int MODE>

@@ -72,9 +72,10 @@ SlidePlan plan_slide(uint32_t nx, uint32_t ny, uint32_t nz) {
   const uint64_t n = (uint64_t)nx * ny * nz;
   // Small grids have too few columns: each workgroup gets two or three planes
   // and computes four or five.  Measured, us per step, single | two per launch:
-  // D3Q19 FP32 64^3 9.0 | 7.9 (k_tile: 7.0), 96^3 28.1 | 16.4; FP64 64^3 17.8 |
-  // 12.9, 96^3 53.8 | 29.9; D3Q27 FP32 64^3 10.7 | 11.6, 96^3 41.2 | 26.8.
-  if (ST == 2 || n < (B::Q == 27 ? 500000u : 1u << 17) || nz < 4) return p;
+  // D3Q19 FP32 117 x 100 x 19 8.3 | 9.4, 64^3 9.0 | 7.9 (k_tile: 7.0), 96^3 28.1 |
+  // 16.4; FP64 64^3 17.8 | 12.9, 96^3 53.8 | 29.9; D3Q27 FP32 64^3 10.7 | 11.6,
+  // 96^3 41.2 | 26.8; FP64 57 x 207 x 61 64 | 75, 63 x 221 x 96 159 | 124.
+  if (ST == 2 || n < (B::Q == 27 ? (ST == 0 ? 1u << 20 : 500000u) : ST == 0 ? 1u << 17 : 1u << 18) || nz < 4) return p;
   if ((uint64_t)nx * ny * sizeof(typename Store<ST>::S) >= 1ull << 32) return p;  // 32-bit byte offsets in a plane
   constexpr uint32_t sx = Sh::PX - 2;
   const uint32_t cx = (nx + sx - 1) / sx, tx = (nx + cx - 1) / cx;
@@ -119,7 +120,9 @@ constexpr bool slide_walls(int q, int eb) { return q == 19 && eb == 4; }
 // the LDS copy of plane p - 1 or, for c_z > 0 (its opposite has one copy only,
 // by now plane p's), in registers kept from the previous iteration.  D3Q19 256^3
 // FP32, walls on the y faces: 703 us for two steps, 2 x 434 by single ones (592
-// without walls: the tiles along a wall are the slowest of the one round).
+// without walls: the tiles along a wall are the slowest of the one round).  Wall
+// terms formed on the host and read from the arguments cost 7 % (scalar loads and
+// spills in the wall wavefronts), a scatter of its own for the others 1 %.
 template <class B, int ST, int MODE, int RLX, bool KEEP, bool WALLS>
 __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs<typename Store<ST>::T> a, SlideArgs g) {
   using L = typename B::Lat;

@@ -98,6 +98,7 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
       for (uint32_t sy : sides) {
         const uint32_t cx = (nx + sx - 1) / sx, cy = (ny + sy - 1) / sy;
         const uint32_t tx = (nx + cx - 1) / cx, ty = (ny + cy - 1) / cy;  // no nearly empty last row
+        if (cx >= 1u << 22) continue;  // a launch holds fewer than 2^32 work-items along x
         const uint64_t rounds = ((uint64_t)cx * cy + 255) / 256;
         double waves = 0;
         for (uint32_t k = 1; k <= kTileMaxSteps; ++k) {

@@ -1263,11 +1263,15 @@ int lbmrv_adjoint(lbmrv_ctx* c, const void* f0, int ut_mode, double ut_alpha, co
     }
   }
   hipStream_t st2 = c->astream;
-  // aev[0]: a snapshot written; aev[1 + r mod 3]: segment r recomputed (on
-  // st2); aev[4 + sg mod 3]: segment sg reversed (on st)
+  // aev[0]: the call's start, then a snapshot written; aev[1 + r mod 3]: segment
+  // r recomputed (on st2); aev[4 + sg mod 3]: segment sg reversed (on st)
   hipEvent_t ev_snap = c->aev[0];
   auto ev_rec = [&](int64_t r) { return c->aev[1 + r % 3]; };
   auto ev_rev = [&](int64_t sg) { return c->aev[4 + sg % 3]; };
+  // st2 starts after what is queued on st: that may still be writing f0 or u~,
+  // or reading this workspace
+  if (recompute_any && (hipEventRecord(ev_snap, st) != hipSuccess || hipStreamWaitEvent(st2, ev_snap, 0) != hipSuccess))
+    return LBMRV_ERR_HIP;
 
   char* w = static_cast<char*>(workspace);
   char* snaps = w;
@@ -1320,7 +1324,7 @@ int lbmrv_adjoint(lbmrv_ctx* c, const void* f0, int ut_mode, double ut_alpha, co
     if (e != hipSuccess) return LBMRV_ERR_HIP;
   }
   if (recompute_any && last - (S - 1) <= 0 && last >= 1) {
-    // segment 0 among them: its first state is f0, present from the start
+    // segment 0 among them: its first state is f0, present since the call's start
     if (issue_recompute(0) != hipSuccess) return LBMRV_ERR_HIP;
   }
   if ((e = fill_zero(partial, P.nblocks * c->q, st)) != hipSuccess) return LBMRV_ERR_HIP;

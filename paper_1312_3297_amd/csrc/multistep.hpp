@@ -91,6 +91,14 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
     // 2.38, 640^2 (30 x 30, 6) 3.3 and (32 x 32, 5) 3.6, 724^2 (28 x 28, 7) 4.3 and
     // (32 x 32, 5) 5.1, 1024^2 (32 x 32, 5) 6.6 and (30 x 30, 6) 7.1.  The search
     // takes some 10 us: once per context.
+    // A wide grid of few rows leaves room for low tiles only (t + steps - 1 <= ny),
+    // a launch of which moves little and mostly waits; there a single step, 3.5 us
+    // and its bytes at 5.8 TB/s (64 lanes to a row of fewer nodes), may be less.
+    // The unit above is 72 ns FP64, 59 FP32 and 31 FP16 over such grids (FP16
+    // regions share a CU by more than two).  us per step, single | tiles: FP64
+    // 77792 x 5 12.0 | 21.9, 286424 x 8 (a field) 59.6 | 99, 30656 x 13 12.8 | 11.2,
+    // FP32 353696 x 7 32 | 51, 58642 x 15 14.3 | 15.1, 29764 x 10 6.3 | 6.0, FP16
+    // 320184 x 5 14.9 | 23.0, 35600 x 13 6.1 | 5.3, 31016 x 30 9.0 | 6.4.
     constexpr bool shared = ST != 0;  // two workgroups fit in a CU's LDS
     constexpr uint32_t sides[] = {32, 30, 28, 24, 20, 16, 12, 8, 4};  // of equal plans the widest in x
     double best = 1e300;
@@ -114,6 +122,9 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
           }
         }
       }
+    constexpr double unit = ST == 0 ? 0.072 : ST == 1 ? 0.059 : 0.031;  // us
+    const double bytes = 2.0 * B::Q * sizeof(typename Store<ST>::S) * ny * (nx < 64 ? 64 : nx);
+    if (unit * best >= 3.5 + bytes / 5.8e6) p.steps = 0;
     return p;
   } else {
     // In space the ring is dear (16 x 8 x 8, two steps: 38 % more node steps;

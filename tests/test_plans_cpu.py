@@ -1,0 +1,21 @@
+"""Which kernel a grid takes (host plans, no GPU), on both sides of the rules."""
+import pytest
+
+from _plans import route
+
+
+# wide grids of few rows: single steps where both sides were measured and they won
+# by more than the rule's 6 %, tiles where tiles won
+@pytest.mark.parametrize("storage,shape,kernel", [
+    ("f64", (5, 77792), "single"), ("f64", (8, 286424), "single"), ("f64", (5, 400000), "single"),
+    ("f64", (12, 256080), "single"), ("f64", (17, 22144), "tile"), ("f64", (19, 147265), "tile"),
+    ("f32", (7, 353696), "single"), ("f32", (6, 33184), "single"), ("f32", (12, 8809), "tile"),
+    ("f32", (25, 164760), "tile"), ("f16dev", (5, 320184), "single"), ("f16dev", (17, 400000), "single"),
+    ("f16dev", (30, 31016), "tile"), ("f16dev", (185, 55074), "tile"),
+    # tall grids of few columns keep tiles: a single step fills 64 lanes per row
+    ("f64", (18108, 5), "tile"), ("f16dev", (7346, 5), "tile"),
+    # and grids of ordinary aspect
+    ("f64", (64, 64), "tile"), ("f32", (2048, 2048), "tile"), ("f16dev", (3089, 2464), "tile")])
+@pytest.mark.parametrize("basis", ["default", "geier"])
+def test_flat_grids_take_the_faster_kernel(storage, shape, kernel, basis):
+    assert route("d2q9", storage, shape, basis)[0] == kernel

@@ -263,14 +263,36 @@ Fused fused_kind(const lbmrv_ctx* c) {
   return slides ? Fused{K_SLIDE, 2} : Fused{K_PUSH, 1};
 }
 
-// nsteps steps p -> q of a two-array form on a grid that k_tile serves (`most`
+// nsteps >= 2 steps p -> q of a two-array form on a grid that k_tile serves (`most`
 // steps per launch), in an odd number of launches so that the last one ends in
 // q: the first reads pre-collision values at the node, the ones between gather
 // and keep post-collision values, the last one scatters pre-collision values.
+// Where full launches leave one step over, that one is a collision in place
+// ahead of them, which is no launch from one array into the other; other even
+// counts take one launch more.  us, shared among one launch more | collision in
+// place: D3Q27 FP32 19 x 19 x 22, 3 steps, 17.3 | 12.9 (single steps 14.4), 32^3, 7
+// steps, 36.5 | 32.8, D2Q9 FP32 2048^2, 6 steps, 255 | 184, 64^2, 9 steps, 15.6 | 13.2.
+// Three FP64 steps in space take a third longer than two, so there it only saves
+// ahead of a single launch (D3Q19 8 x 14 x 12: 4 steps 17.2 | 16.0, 10 steps 33.9 |
+// 36.9).  A share of one step stays with k_tile: a single step would be another
+// kernel, whose instructions the CUs have to fetch (D3Q27 FP64 15 x 11 x 18, 12
+// steps: 54.0, with two single steps 58.4).
 hipError_t run_tiles(const lbmrv_ctx* c, int64_t most, void* p, void* q, int64_t nsteps, int mode, double alpha,
                      const float* ut, hipStream_t st) {
   int64_t launches = (nsteps + most - 1) / most;
-  if (launches % 2 == 0) ++launches;  // an even count has at least launches + 1 steps to share
+  bool collided = false;  // p holds post-collision values
+  hipError_t e;
+  if (launches % 2 == 0) {
+    const bool dear = c->d == 3 && c->storage == LBMRV_F64 && most > 2;
+    if (nsteps - 1 == (launches - 1) * most && !(dear && launches > 2)) {
+      if ((e = run_kind(c, K_COLLIDE, p, p, mode, alpha, ut, st)) != hipSuccess) return e;
+      collided = true;
+      --nsteps;
+      --launches;
+    } else {
+      ++launches;  // an even count has at least launches + 1 steps to share
+    }
+  }
   StepLaunch L = base_launch(c, st);
   L.kind = K_TILE;
   L.mode = mode;
@@ -280,10 +302,9 @@ hipError_t run_tiles(const lbmrv_ctx* c, int64_t most, void* p, void* q, int64_t
     L.fin = i % 2 == 0 ? p : q;
     L.fout = i % 2 == 0 ? q : p;
     L.steps = (uint32_t)(nsteps / launches + (i < nsteps % launches ? 1 : 0));
-    L.gather = i > 0;
+    L.gather = collided || i > 0;
     L.scatter = i + 1 == launches;
-    hipError_t e = kEntries[c->entry].step[c->sk](L);
-    if (e != hipSuccess) return e;
+    if ((e = kEntries[c->entry].step[c->sk](L)) != hipSuccess) return e;
   }
   return hipSuccess;
 }

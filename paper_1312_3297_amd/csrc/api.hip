@@ -251,12 +251,12 @@ struct Fused {
 Fused fused_kind(const lbmrv_ctx* c) {
   const bool slides = c->slide.chunk != 0;
   if (c->wall_mask) {
-    // k_slide has walls on x and y faces, for the built-in bases; on both faces of
-    // an axis, as its last launch scatters (past a single wall, the slot a node
-    // bounces into would also be reached through the open face)
+    // k_slide has walls on x and y faces; on both faces of an axis, as its last
+    // launch scatters (past a single wall, the slot a node bounces into would also
+    // be reached through the open face)
     const uint32_t m = c->wall_mask;
     const bool paired = (m & 1u) == ((m >> 1) & 1u) && ((m >> 2) & 1u) == ((m >> 3) & 1u);
-    if (slides && !(m >> 4) && paired && !c->custom && slide_walls(c->q, (int)elem_bytes(c->storage))) return {K_SLIDE, 2};
+    if (slides && !(m >> 4) && paired && slide_walls(c->q, (int)elem_bytes(c->storage))) return {K_SLIDE, 2};
     return {K_PUSH, 1};
   }
   if (c->tile.steps >= 2) return {K_TILE, c->tile.steps};
@@ -694,6 +694,28 @@ const void* tab_ptr(const lbmrv_ctx* c, int which) {
   return c->custom ? static_cast<const char*>(c->dtab) + tab_offset(c, which) : nullptr;
 }
 
+// Where a run-time basis takes several steps per launch.  In space its dense
+// relaxation (15^2 or 23^2 multiplications a node) makes ring nodes dear, and the
+// matrix and the node do not fit in the registers that k_slide has left, so it has
+// no such instances: us, 21 steps, single | pairs, D3Q27 FP32 96^3 947 | 1925,
+// D3Q19 FP64 150 x 131 x 140 4612 | 7737, FP32 2394 | 3091.  Tiles pay up to 8 x 4 x 4
+// nodes, beyond 64 with the ring of two steps (20 steps: D3Q19 FP32 64^3, 16 x 8 x 8,
+// 0.77 times the speed of single steps, 48^3, 12 x 6 x 6, 0.85, FP64 0.81; FP16 32^3,
+// 8 x 4 x 4, four steps 0.81; 4 x 4 x 4 1.05 to 1.6), D3Q27 FP64 up to 16^3 (1.07 to
+// 1.3, 20^3 with u~ = u 0.89).
+void plan_custom(lbmrv_ctx* c) {
+  if (c->d != 3) return;
+  c->slide = SlidePlan{};
+  TilePlan& p = c->tile;
+  const uint32_t nodes = p.t[0] * p.t[1] * p.t[2];
+  if (nodes > 128 || (c->q == 27 && c->storage == LBMRV_F64 && c->N > 4096)) {
+    p.steps = 0;
+  } else if (nodes > 64 && p.steps > 2) {
+    p.steps = 2;
+    p.threads = ((p.t[0] + 2) * (p.t[1] + 2) * (p.t[2] + 2) + 63) / 64 * 64;
+  }
+}
+
 // A context with a run-time basis must be used on the device its table lives on.
 int check_device(const lbmrv_ctx* c) {
   if (!c->custom) return LBMRV_OK;
@@ -769,6 +791,7 @@ int lbmrv_create_custom(lbmrv_ctx** out, int lattice, const lbmrv_poly_basis* ba
     return rc;
   c->basis = LBMRV_BASIS_CUSTOM;
   c->custom = 1;
+  plan_custom(c);
   c->R = std::move(R);
   c->Rnn = std::move(Rnn);
   c->Rnninv = std::move(Rnninv);

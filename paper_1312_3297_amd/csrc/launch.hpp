@@ -180,24 +180,25 @@ hipError_t launch_tile_t(const StepLaunch& L) {
   return hipGetLastError();
 }
 
-template <class B, int ST, int MODE, int RLX>
+// built-in bases only (plan_custom)
+template <class B, int ST, int MODE>
 hipError_t launch_slide_t(const StepLaunch& L) {
   if constexpr (B::Lat::D == 3 && ST != 2) {
     const SlidePlan& p = L.slide;
-    if (!p.chunk) return hipErrorInvalidValue;
+    if (!p.chunk || L.relax) return hipErrorInvalidValue;
     SlideArgs g{{p.t[0], p.t[1]}, p.chunk, L.gather, L.scatter, L.keep};
     StepArgs<typename Store<ST>::T> a = step_args<ST>(L);
     dim3 grid((L.nx + p.t[0] - 1) / p.t[0], (L.ny + p.t[1] - 1) / p.t[1], (L.nz + p.chunk - 1) / p.chunk);
     const dim3 threads(p.threads);
     if (L.wall_mask) {
-      if constexpr (slide_walls(B::Q, (int)sizeof(typename Store<ST>::S)) && RLX == 0) {
-        hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false, true>), grid, threads, 0, L.stream, a, g);
+      if constexpr (slide_walls(B::Q, (int)sizeof(typename Store<ST>::S))) {
+        hipLaunchKernelGGL((k_slide<B, ST, MODE, false, true>), grid, threads, 0, L.stream, a, g);
         return hipGetLastError();
       }
       return hipErrorInvalidValue;
     }
-    if (L.keep) hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, true, false>), grid, threads, 0, L.stream, a, g);
-    else hipLaunchKernelGGL((k_slide<B, ST, MODE, RLX, false, false>), grid, threads, 0, L.stream, a, g);
+    if (L.keep) hipLaunchKernelGGL((k_slide<B, ST, MODE, true, false>), grid, threads, 0, L.stream, a, g);
+    else hipLaunchKernelGGL((k_slide<B, ST, MODE, false, false>), grid, threads, 0, L.stream, a, g);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -221,7 +222,7 @@ hipError_t launch_step_m(const StepLaunch& L) {
   if (L.kind == K_TILE)
     return L.relax ? launch_tile_t<B, ST, MODE, 1>(L) : launch_tile_t<B, ST, MODE, 0>(L);
   if (L.kind == K_SLIDE)
-    return L.relax ? launch_slide_t<B, ST, MODE, 1>(L) : launch_slide_t<B, ST, MODE, 0>(L);
+    return launch_slide_t<B, ST, MODE>(L);
   if (L.relax) {  // run-time basis: the two-array forms
     switch (L.kind) {
       case K_PULL: return launch_step_t<B, ST, MODE, K_PULL, 1>(L);

@@ -123,7 +123,7 @@ constexpr bool slide_walls(int q, int eb) { return q == 19 && eb == 4; }
 // without walls: the tiles along a wall are the slowest of the one round).  Wall
 // terms formed on the host and read from the arguments cost 7 % (scalar loads and
 // spills in the wall wavefronts), a scatter of its own for the others 1 %.
-template <class B, int ST, int MODE, int RLX, bool KEEP, bool WALLS>
+template <class B, int ST, int MODE, bool KEEP, bool WALLS>
 __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs<typename Store<ST>::T> a, SlideArgs g) {
   using L = typename B::Lat;
   using S = typename Store<ST>::S;
@@ -260,7 +260,7 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
         });
       }
     }
-    collide_node<B, T, MODE, RLX>(h, a, uc);
+    collide_node<B, T, MODE, 0>(h, a, uc);
     S o[Q];
     sfor<Q>([&](auto jj) { o[jj] = S(h[jj]); });
     if (column) {
@@ -324,7 +324,7 @@ __global__ __launch_bounds__((SlideShape<B, ST>::threads)) void k_slide(StepArgs
           pop += stride;
         });
       }
-      collide_node<B, T, MODE, RLX>(h, a, up);
+      collide_node<B, T, MODE, 0>(h, a, up);
       sfor<Q>([&](auto jj) { o[jj] = S(h[jj]); });
       const int zm = wrapz(z - 1), zp = wrapz(z + 1);
       const uint64_t bz = (uint64_t)z * plane, bm = (uint64_t)zm * plane, bp = (uint64_t)zp * plane;

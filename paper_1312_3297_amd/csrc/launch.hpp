@@ -112,13 +112,20 @@ hipError_t launch_step_t(const StepLaunch& L) {
   // D3Q19 keeps 256-wide rows (four per block in FP32) on wider grids too:
   // at 512^3 that measured 6.9 % faster than 512-wide rows in FP32, 3.9 % in
   // FP64 and the same in FP16.
+  // D2Q9 in FP64 (pair form, 70 VGPRs, seven wavefronts per SIMD) takes blocks of
+  // 256 threads, seven to a CU instead of three of 512; only rows of 257 to 511
+  // nodes keep one block each.  us, 512 | 256 threads: walls, 7 steps, 518 x 497 92.9
+  // | 64.4, 640 x 333 66 | 51, 4000 x 3000 2447 | 2372, 2048^2 878 to 936 | 853 to 945
+  // by allocation, 385 x 700 69.3 | 74.0; in place, 20 steps, 300 x 301 105 | 99, 640 x
+  // 333 133 | 126.
   constexpr bool wide = KIND == K_PULL || KIND == K_STREAM || KIND == K_COLLIDE;
-  const uint32_t bx_max = !wide ? 256u : (B::Q == 19 ? 256u : (uint32_t)step_max_threads<ST, KIND>());
+  constexpr bool small_blocks = B::Lat::D == 2 && ST == 0;
+  const uint32_t bx_max = !wide || B::Q == 19 || (small_blocks && L.nx >= 512u) ? 256u : (uint32_t)step_max_threads<ST, KIND>();
   const uint32_t bx = L.nx >= bx_max ? bx_max : ((L.nx + 63u) / 64u) * 64u;
   // (FP16 storage measured faster with one row per block)
   uint32_t by = (KIND == K_PUSH || KIND == K_AA_ODD || KIND == K_AA_ODD_WALLS || ST == 2)
                     ? 1u
-                    : (uint32_t)step_max_threads<ST, KIND>() / bx;
+                    : (small_blocks ? (bx > 256u ? bx : 256u) : (uint32_t)step_max_threads<ST, KIND>()) / bx;
   // D3Q27's step holds ~90 VGPRs, so at most 5 wavefronts per SIMD: one
   // 15-wavefront block of five 192-wide rows per CU leaves slots idle, blocks
   // of two rows pack better (measured +2.6 % at 192^3 FP32; one row and three

@@ -38,3 +38,34 @@ def route(lattice, storage, shape, basis="default"):
         return ("tile", tuple(t.t), t.steps)
     s = _call("plan_slide", SlidePlan, lattice, storage, shape, basis)
     return ("slide", tuple(s.t), s.chunk) if s.chunk else ("single",)
+
+
+# Grids (nz, ny, nx) that take a kernel of several steps per launch, with what
+# each is there for; the GPU tests compare them with single steps, the CPU test
+# holds every one to the route it names.
+FUSED = [
+    # two steps per launch: few planes, a short last chunk, tiles that divide the
+    # extents and that leave a remainder in x, y and z, rows of each number
+    ("d3q19", "f32", (5, 230, 232), "slide"), ("d3q19", "f32", (131, 45, 64), "slide"),
+    ("d3q19", "f32", (70, 64, 64), "slide"), ("d3q19", "f32", (67, 65, 63), "slide"),
+    ("d3q19", "f32", (16, 171, 128), "slide"), ("d3q19", "f64", (5, 161, 193), "slide"),
+    ("d3q19", "f64", (70, 64, 64), "slide"), ("d3q19", "f64", (49, 53, 57), "slide"),
+    ("d3q27", "f32", (101, 77, 90), "slide"), ("d3q27", "f32", (7, 305, 257), "slide"),
+    ("d3q27", "f32", (80, 80, 81), "slide"), ("d3q27", "f64", (102, 101, 103), "slide"),
+    ("d3q27", "f64", (4, 513, 520), "slide"), ("d3q27", "f64", (104, 104, 98), "slide"),
+    # the larger tiles in space: 12 x 6 x 6 and 16 x 8 x 8
+    ("d3q19", "f32", (48, 48, 48), "tile 12 6 6"), ("d3q19", "f32", (47, 46, 48), "tile 12 6 6"),
+    ("d3q19", "f64", (48, 48, 48), "tile 12 6 6"), ("d3q19", "f64", (42, 41, 47), "tile 12 6 6"),
+    ("d3q19", "f16dev", (48, 48, 48), "tile 12 6 6"), ("d3q19", "f16dev", (47, 46, 48), "tile 12 6 6"),
+    ("d3q19", "f32", (64, 64, 61), "tile 16 8 8"), ("d3q19", "f32", (59, 62, 63), "tile 16 8 8"),
+]
+
+
+def is_route(lattice, storage, shape, want):
+    """Whether a grid's plan is the kernel (and the tile of at most the sides) named."""
+    r = route(lattice, storage, shape)
+    kind, *sides = want.split()
+    if r[0] != kind:
+        return False
+    # equal tiles of at most side nodes: -(-n // -(-n // side))
+    return all(t == -(-n // -(-n // int(s))) for t, n, s in zip(r[1], reversed(shape), sides))

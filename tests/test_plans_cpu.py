@@ -1,7 +1,7 @@
 """Which kernel a grid takes (host plans, no GPU), on both sides of the rules."""
 import pytest
 
-from _plans import route
+from _plans import FUSED, is_route, route
 
 
 # wide grids of few rows: single steps where both sides were measured and they won
@@ -19,3 +19,16 @@ from _plans import route
 @pytest.mark.parametrize("basis", ["default", "geier"])
 def test_flat_grids_take_the_faster_kernel(storage, shape, kernel, basis):
     assert route("d2q9", storage, shape, basis)[0] == kernel
+
+
+@pytest.mark.parametrize("lattice,storage,shape,want", FUSED)
+def test_the_compared_grids_take_the_kernels_they_are_listed_for(lattice, storage, shape, want):
+    assert is_route(lattice, storage, shape, want), route(lattice, storage, shape)
+
+
+def test_every_instance_is_compared():
+    slides = {(la, s) for la, s, _, w in FUSED if w == "slide"}
+    assert slides == {("d3q19", "f32"), ("d3q19", "f64"), ("d3q27", "f32"), ("d3q27", "f64")}
+    chunks = [route(la, s, sh)[2] for la, s, sh, w in FUSED if w == "slide"]
+    assert any(sh[0] % c for (_, _, sh, w), c in zip([f for f in FUSED if f[3] == "slide"], chunks))  # a short last chunk
+    assert min(sh[0] for _, _, sh, w in FUSED if w == "slide") == 4                                    # the fewest planes

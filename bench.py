@@ -14,8 +14,9 @@ the algorithmic bytes of one step (2 q b per node, plus the u~ field when it is
 read) over the measured time per step; roofline.per_launch gives the same per
 kernel launch of the in-place form (they differ only by its final swap after
 an odd step count).  With two arrays (--streaming pull or push) the library
-takes several steps per launch where that is faster, so one launch is no fixed
-number of steps and per_launch is null.
+takes several steps per launch where that is faster: the state then crosses HBM
+once per launch, the bytes of a step over its time are no traffic and HBM is not
+the bound, so bound, achieved, frac and per_launch are null (traffic too).
 """
 import argparse
 import json
@@ -36,7 +37,8 @@ HBM_PEAK_GBS = 8000.0
 # a plain copy of known size (FETCH x 2.0, WRITE x 1.0); see profiles/.  Only
 # valid for the kernel version the counters were taken on, in the default
 # (automatic) block order; the in-place form averages its two kernels.  With two
-# arrays only the FP16 workloads still take one step per launch.
+# arrays only the workloads listed here take one step per launch (in space FP16
+# storage, and run-time bases).
 TRAFFIC_GB = {
     ("d2q9_shear2048_f32_fluid", "aa"): 0.3021,
     ("d2q9_shear4096_f32_fluid", "aa"): 1.2395,
@@ -50,6 +52,7 @@ TRAFFIC_GB = {
     ("d3q27_tgv192_f16dev_field", "aa"): 0.8495,
     ("d3q27_tgv192_f32_field", "aa"): 1.6143,
     ("d3q19_tgv256_f16dev_fluid", "pull"): 1.2752,
+    ("d3q19_tgv256_f32_fluid_rawbasis", "pull"): 2.5512,
     ("d3q27_tgv192_f16dev_field", "pull"): 0.8731,
 }
 
@@ -259,6 +262,24 @@ def side_kernels(ctx, f, b, torch, reps=20):
     return res
 
 
+def roofline(name, streaming, block_order, bytes_per_step, steps, ms):
+    """The roofline block of `steps` steps in `ms`: rates per step, and per launch
+    of the in-place form (K launches and one swap pass when K is odd, a little
+    smaller)."""
+    r = {"bound": None, "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
+         "traffic": TRAFFIC_GB.get((name, streaming)) if block_order == "auto" else None,
+         "bytes_per_step_GB": round(bytes_per_step / 1e9, 4), "per_launch": None}
+    if streaming == "aa" or (name, streaming) in TRAFFIC_GB:  # one step per launch
+        achieved = bytes_per_step * steps / (ms * 1e-3) / 1e9
+        r.update(bound="hbm", achieved=round(achieved, 1), frac=round(achieved / HBM_PEAK_GBS, 4))
+    if streaming == "aa":
+        launches = steps + steps % 2
+        achieved = bytes_per_step * launches / (ms * 1e-3) / 1e9
+        r["per_launch"] = {"launches": launches, "achieved": round(achieved, 1),
+                           "frac": round(achieved / HBM_PEAK_GBS, 4)}
+    return r
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -324,13 +345,7 @@ def main():
     N = ctx.N
     q = ctx.q
     b = {"f64": 8, "f32": 4, "f32dev": 4, "f16dev": 2}[storage]
-    # kernel launches inside the call: in place K (+ one swap pass when K is odd;
-    # every launch reads and writes q populations per node, the swap pass a little
-    # less); with two arrays the library's choice
-    launches = K + (K % 2) if args.streaming == "aa" else None
     bytes_per_step = 2 * q * b * N + (ctx.d * 4 * N if mode == "field" else 0)
-    achieved = bytes_per_step * K / (ms * 1e-3) / 1e9
-    achieved_launch = bytes_per_step * launches / (ms * 1e-3) / 1e9 if launches else None
     mlups = N * K / (ms * 1e-3) / 1e6
     out = {
         "metric": METRIC,
@@ -348,12 +363,7 @@ def main():
         "config": {"workload": name, "lattice": lattice, "grid": list(dims), "storage": storage,
                    "relative_velocity": mode, "streaming": args.streaming, "block_order": args.block_order,
                    "nodes": N},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": TRAFFIC_GB.get((name, args.streaming)) if args.block_order == "auto" else None,
-                     "bytes_per_step_GB": round(bytes_per_step / 1e9, 4),
-                     "per_launch": {"launches": launches, "achieved": round(achieved_launch, 1),
-                                    "frac": round(achieved_launch / HBM_PEAK_GBS, 4)} if launches else None},
+        "roofline": roofline(name, args.streaming, args.block_order, bytes_per_step, K, ms),
         "state_finite": bool(finite),
         "wall_s": round(wall, 4),
     }

@@ -175,11 +175,12 @@ int lbmrv_set_rates(lbmrv_ctx *c, const double *s);
  *     f_in == f_out (otherwise f_in is first copied to f_out).
  * With two arrays a call of several steps takes as many per kernel launch as
  * suit the grid, whichever of the two forms is selected (the order of the
- * launches is then the library's own): 2-D grids and small 3-D ones 2 to 8,
- * larger 3-D ones in FP64 and FP32 storage 2, with walls only D3Q19 in FP32
- * storage and walls on both faces of the x or y axis.  Grids of at most 512
- * nodes take all steps in one launch, in every form (in place without the
- * copy of f_in).  f_in is overwritten as before.
+ * launches is then the library's own): 2-D grids of more than a few rows and
+ * small 3-D ones 2 to 8, larger 3-D ones in FP64 and FP32 storage 2 (with a
+ * run-time basis only small ones), with walls only D3Q19 in FP32 storage and
+ * walls on both faces of the x or y axis.  Without walls, grids of at most 512
+ * nodes take up to 4096 steps per launch, in every form (in place without the
+ * copy of f_in).  With two arrays f_in may be overwritten.
  * No HIP call.
  */
 int lbmrv_set_streaming(lbmrv_ctx *c, int kind);
@@ -369,8 +370,8 @@ int lbmrv_lattice_tables(int lattice, int32_t *cdirs, double *w);
  * segments are recomputed on a second stream that the context creates at its
  * first such call (default priority, on the device current then; a later
  * call on another device returns INVALID_ARG) and orders against hip_stream
- * with events: all of that work is complete before anything enqueued on
- * hip_stream after the call runs.  Errors: INVALID_ARG, UNSUPPORTED,
+ * with events: that work starts after what was enqueued on hip_stream before
+ * the call and is complete before anything enqueued on it after the call runs.  Errors: INVALID_ARG, UNSUPPORTED,
  * ALIGNMENT, HIP.
  */
 size_t lbmrv_adjoint_workspace_bytes(const lbmrv_ctx *c, int64_t nsteps, int64_t K);

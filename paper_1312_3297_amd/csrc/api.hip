@@ -1198,8 +1198,8 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // has that kernel.  Up to 2^21 nodes: small grids are bound by each launch's
 // latency and fixed cost.  Beyond 2^22 with u~ a field: there the single step
 // moves 148 bytes per node from HBM and two in one launch 110 each, and the
-// states no longer fit in the last-level cache; without the field's 24 bytes the
-// vector ALU weighs as much.  us for two steps, one | two per launch, D2Q9 FP32,
+// states no longer fit in the last-level cache; without the field's 40 bytes a
+// launch (u~ read, its gradient read and written) the vector ALU weighs as much.  us for two steps, one | two per launch, D2Q9 FP32,
 // a field: 512^2 15.3 | 12.2, 1448^2 86.0 | 86.4, 2048^2 162 | 175, 2900^2 428 |
 // 370, 4096^2 816 | 662; u~ = u: 512^2 13.7 | 11.1, 1448^2 72 | 76, 2048^2 135 |
 // 149, 2900^2 293 | 313, 4096^2 584 | 560.  Up to 2^28 nodes, as the kernel's

@@ -135,6 +135,11 @@ TilePlan plan_tile(uint32_t nx, uint32_t ny, uint32_t nz) {
     //   D3Q19 FP32  16^3 5.1 | 2.6  32^3 5.2 | 3.2  48^3 5.9 | 5.0  64^3 9.0 | 7.0
     //   D3Q19 FP64  16^3 6.5 | 3.0  32^3 6.0 | 4.4  48^3 10.4 | 7.3
     //   D3Q27 FP32  16^3 6.0 | 4.2  32^3 5.5 | 4.8  48^3 7.2 | 7.4
+    // and of FP16 and D3Q27 FP64, us per step of single scatter passes, the fastest of
+    // the single steps | by launches of the most steps, u~ = u:
+    //   D3Q19 FP16  9 x 8 x 8 3.9 | 2.5  16^3 3.9 | 2.5  32^3 3.8 | 3.3  48^3 5.1 | 4.3
+    //   D3Q27 FP16  9 x 8 x 8 4.3 | 3.5  16^3 4.3 | 3.5  27 x 25 x 20 4.2 | 3.7
+    //   D3Q27 FP64  9 x 8 x 8 5.1 | 4.3  16^3 5.3 | 4.5  27 x 25 x 20 5.2 | 5.3
     // A fused pass takes its time however many of the 256 CUs it fills, a single
     // one less on a smaller grid, hence the least nodes of the larger tiles: D3Q19
     // FP32 101 x 49 x 15 (12 x 6 x 6) 4.9 | 5.9, 64 x 20 x 73 (16 x 8 x 8) 4.8 |
@@ -340,7 +345,9 @@ __global__ __launch_bounds__((TileShape<B, ST>::threads)) void k_tile(StepArgs<t
 // first store to fout, so the two may be the same array.  A step costs the
 // latency of one collision and one LDS exchange, which a second wavefront per
 // SIMD hides half of; D2Q9 16^2 FP64, 50 steps: 32 us, and 82 by k_tile (7
-// launches).
+// launches).  At 512 nodes, us for 20 steps, single steps | one launch: D2Q9 16 x 32
+// FP64 78 | 21, D3Q19 8^3 FP32 82 | 29, FP16 86 | 30, D3Q27 8^3 FP32 91 | 44, FP16 104 |
+// 45, FP64 (110 KB of LDS) 107 | 71; two steps of the last 14.9 | 10.3.
 constexpr uint32_t kClosedNodes = 512;
 
 template <class B, int ST, int MODE>
